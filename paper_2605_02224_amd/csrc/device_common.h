@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <string>
 
@@ -108,6 +110,9 @@ inline void fill_cloud_args(const mknn_cloud *c, QueryArgs *a) {
   a->hy = c->dev_hxyz[1];
   a->hz = c->dev_hxyz[2];
   a->n = c->dev_n;
+  double ext = 0.0;
+  for (int k = 0; k < 3; ++k) ext = std::max(ext, (double)c->dev_hi[k] - (double)c->dev_lo[k]);
+  a->key_scale = ext > 0.0 ? std::ldexp(1.0, -2 * std::ilogb(ext)) : 1.0;
 }
 
 // A list change in two steps: delete_prepare / insert_prepare edit the host lists and
@@ -144,9 +149,23 @@ extern "C" mknn_status mknn_upload(mknn_cloud *c, void *stream);
 // A launch configuration of the query kernels (see mknn_device.hip).
 struct TuneConfig {
   int32_t family;      // 1 lane per query, 2 lockstep rows, 3 scheduled rows
-  int32_t merge_min;   // k <= 16: candidates per chunk from which the merge network is used
-  int32_t per_wave;    // row kernel: queries per wavefront
+  int32_t merge_min;   // families 2, 3: candidates per chunk from which the merge network is used
+  int32_t per_wave;    // family 3: queries per wavefront
 };
+
+// How the wave kernel lays nq queries out: lanes per query in the descent, and queries per
+// wavefront (at most 64 / lanes; a second one only once every resident wavefront has one).
+struct WaveShape {
+  int32_t lanes, per_wave;
+};
+inline WaveShape wave_shape(int64_t nq, int kmax) {
+  const int64_t resident = 32 * (int64_t)device_cus();
+  WaveShape w;
+  w.lanes = kmax <= 32 && nq >= 8 * resident ? 8 : 16;
+  w.per_wave = 1;
+  while (w.per_wave * 2 <= 64 / w.lanes && nq > w.per_wave * resident) w.per_wave *= 2;
+  return w;
+}
 TuneConfig config_for(int kmax, bool exact, int64_t n);
 
 // Optional HIP-event timing of the main query kernels (defined in mknn_device.hip).

@@ -5,7 +5,8 @@
 //   ent[]  16-byte records {x, y, z, rank} (float, float, float, int32 bit pattern).  The
 //          entries of list L_i are contiguous and ascending in rank (Sec. 3); whole lists
 //          are placed in the Morton order of their owner points.  The array is padded with
-//          kEntPad records so a 16-lane chunk may reach 15 records past the end of a list.
+//          kEntPad records: a 16-lane chunk may reach 15 records past the end of a list, a
+//          64-lane batch 63.
 //   lst[r] 64-bit descriptor: start index of L_r in ent (low 32 bits) | length (high 32).
 // Each list entry carries its point's coordinates, so scanning a list is one contiguous
 // read and no second gather is needed to evaluate the distance.
@@ -15,7 +16,7 @@
 
 namespace mknn {
 
-constexpr int kEntPad = 16;
+constexpr int kEntPad = 64;
 constexpr int32_t kEmpty = 0x7fffffff;   // rank of an empty candidate slot
 
 struct QueryArgs {
@@ -47,6 +48,7 @@ struct QueryArgs {
   uint32_t epoch;
   int32_t kout;
   uint32_t *overflow;
+  double key_scale;   // power of two that maps the square of the cloud's extent near 1
   // Other layouts of the same lists, for the measurement that compares them with the
   // records above (only the layout kernel reads these): rk[i] is the rank of record i;
   // ranks only: pts[r] is the point of rank r; four arrays: sx, sy, sz[i] are the

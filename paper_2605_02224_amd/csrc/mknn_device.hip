@@ -2,12 +2,14 @@
 // the query kernels and their launch configuration (with the autotuner's table), list
 // deltas for deletion and insertion, and the plane fit.
 //
-// Three kernel families compute the same rows (the 1-NN descent of Alg. 1, the k-expansion
+// Four kernel families compute the same rows (the 1-NN descent of Alg. 1, the k-expansion
 // of Alg. 2, the prefix bound of Sec. 4.2), with identical float64 keys (D, rank):
 //   lane  (knn_lane_kernel, below): one query per lane, N a register-resident sorted array;
 //   group (knn_group.h): 16 lanes per query, the four rows of a wavefront in lockstep phases
 //         (it also carries the work-counting variant);
-//   rows  (knn_rows.h): 16 lanes per query, rows scheduled independently -- the default.
+//   rows  (knn_rows.h): 16 lanes per query, rows scheduled independently;
+//   wave  (knn_wave.h): descents side by side, expansions one query per wavefront.
+// use_wave() chooses between the last two.
 // In the lane kernel every examined entry, transition sites included, is offered to N;
 // offering more true sites than Alg. 1 does never changes the result, and it lets the
 // final, completely scanned list of the descent serve as Alg. 2's first iteration.
@@ -29,6 +31,7 @@
 #include "device_common.h"
 #include "knn_group.h"
 #include "knn_rows.h"
+#include "knn_wave.h"
 #include "planefit.h"
 
 namespace mknn {
@@ -211,6 +214,17 @@ constexpr int kScanBlock = 1024;
 constexpr int kScanBlocks = kMortonBins / kScanBlock;
 static_assert(kScanBlocks <= 1024, "one workgroup scans the block totals");
 constexpr int64_t kSortMinQueries = 8192;
+// Up to this many queries the wave kernel is the faster one at every k (see use_wave()).
+constexpr int64_t kLargeQueries = 65536;
+// The wave kernel gains less from neighbours in a wavefront than the bucketing costs (five
+// launches, 20 us and up) until launches are larger: 1M-point torus, k = 16, 65536 queries 182
+// us as they come, 215 us bucketed; 262144 queries 594 and 590; 1000000 queries 2081 and 1928.
+// With long rows, or the plane fit's gather of their points, it pays from half as many: 200k
+// queries over 200k points, k = 64 1.42 and 1.33 ms, k = 20 with planes 714 and 692 us.
+constexpr int64_t kWaveSortQueries = 262144;
+static int64_t wave_sort_min(int kmax, bool planes) {
+  return kmax > 32 || planes ? kWaveSortQueries / 2 : kWaveSortQueries;
+}
 
 // The histogram's atomic hands every query its rank within its bin, so the scatter below
 // places it with no atomic of its own.
@@ -562,18 +576,34 @@ hipError_t timing_mark(hipStream_t s, bool start) {
 // candidates per chunk from which k <= 16 merges with the network instead of inserting one
 // by one, and the queries per wavefront of the row kernel.  mknn_autotune fills a table
 // keyed by (device, slots per lane S, k == 16 S, log2 n); launches look their key up and
-// fall back to the measured defaults.  Environment variables override both (experiments).
+// fall back to the measured defaults, but for those that the wave kernel takes for their
+// size.  Environment variables override all of it (experiments).
 // ---------------------------------------------------------------------------------------
 static long env_long(const char *name, long dflt) {
   const char *e = getenv(name);
   return e ? atol(e) : dflt;
 }
 
-// Defaults measured on the 1M torus: scheduled rows, one query per row, and the merge
-// network from 6 / 8 / 8 / 8 candidates per chunk for S = 1..4 slots per lane.
-static TuneConfig default_config(int S) {
-  static const int32_t mm[4] = {8, 8, 8, 8};
-  return {3, mm[(S < 1 ? 1 : S > 4 ? 4 : S) - 1], 4};
+// Untuned launches by rows, measured on the 1M torus: one query per row, and the merge network
+// from 8 candidates per chunk on.
+constexpr TuneConfig kDefaultConfig = {3, 8, 4};
+
+// Rows or wavefronts.  The wave kernel's steps are short (a query's critical path is half the
+// row kernel's), the row kernel's lanes are fuller for short rows of many queries.  us per
+// launch over a 1M-point torus, rows (bucketed) / wave (bucketed from kWaveSortQueries on):
+//   queries      k=1         k=8          k=16         k=20         k=32         k=64
+//   10000       51 / 26     69 / 43      89 / 52     111 / 58     140 / 72     248 / 168
+//   32768       51 / 34     90 / 77     122 / 102    152 / 114    195 / 152    375 / 327
+//   65536       76 / 50    136 / 134    188 / 182    241 / 207    312 / 277    633 / 525
+//   98304      101 / 81    182 / 200    255 / 268    328 / 305    433 / 407    899 / 708
+//   262144     213 / 172   397 / 430    567 / 590    730 / 676    990 / 917   2071 / 1591
+//   1000000    695 / 534  1388 / 1433  1947 / 1928  2507 / 2199  3373 / 2974  7195 / 5374
+// With a k and prefix per query many lists end early in their prefix and leave the wave
+// kernel's batches half empty: 300k queries of k <= 12, rows 1.70 ms, wave 1.78 ms.
+static bool use_wave(int kmax, bool exact, int64_t nq) {
+  static const char *const v = getenv("MKNN_KERNEL");
+  if (v) return v[0] == 'w';
+  return nq <= kLargeQueries || (exact && (kmax == 1 || kmax > 16));
 }
 
 static std::mutex g_tune_mu;
@@ -604,7 +634,7 @@ TuneConfig config_for(int kmax, bool exact, int64_t n) {
   const int S = (kmax + 15) / 16;
   int dev = 0;
   (void)hipGetDevice(&dev);
-  TuneConfig c = default_config(S);
+  TuneConfig c = kDefaultConfig;
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tune.find(tune_key(dev, S, exact && kmax == 16 * S, n));
@@ -711,7 +741,24 @@ static hipError_t dispatch_rows(const QueryArgs &a, int kmax, bool exact, int32_
   return hipErrorInvalidValue;
 }
 
-// Bytes of scratch the Morton bucketing of nq queries needs (0 below the sort threshold).
+template <int DW, int R>
+static hipError_t launch_wave(const QueryArgs &a, int32_t per_wave, hipStream_t s) {
+  const int64_t waves = (a.nq + per_wave - 1) / per_wave;
+  const uint32_t blocks = (uint32_t)((waves + 3) / 4);
+  hipLaunchKernelGGL((knn_wave_kernel<DW, R>), dim3(blocks), dim3(256), 0, s, a, per_wave);
+  return hipGetLastError();
+}
+
+static hipError_t dispatch_wave(const QueryArgs &a, int kmax, hipStream_t s) {
+  const WaveShape w = wave_shape(a.nq, kmax);
+  if (kmax <= 16)
+    return w.lanes == 8 ? launch_wave<8, 16>(a, w.per_wave, s) : launch_wave<16, 16>(a, w.per_wave, s);
+  if (kmax <= 32)
+    return w.lanes == 8 ? launch_wave<8, 32>(a, w.per_wave, s) : launch_wave<16, 32>(a, w.per_wave, s);
+  return launch_wave<16, 64>(a, w.per_wave, s);
+}
+
+// Bytes of scratch the Morton bucketing of nq queries may need (0 below every sort threshold).
 static size_t sort_scratch_bytes(int64_t nq) {
   return nq < kSortMinQueries ? 0
                               : sizeof(uint32_t) * (kMortonBins + kScanBlocks) +
@@ -722,11 +769,11 @@ static size_t sort_scratch_bytes(int64_t nq) {
 // (sort_scratch_bytes(nq), 256-byte aligned) comes from `fixed` when given, else from the
 // stream-ordered allocator (returned in *scratch for the caller to release).
 static mknn_status prepare_queries(const mknn_cloud *c, const float *d_q, int64_t nq,
-                                   hipStream_t s, float4 **qs_out, void **scratch,
+                                   hipStream_t s, int64_t sort_min, float4 **qs_out, void **scratch,
                                    void *fixed = nullptr) {
   *qs_out = nullptr;
   *scratch = nullptr;
-  if (nq < kSortMinQueries) return MKNN_OK;
+  if (nq < sort_min) return MKNN_OK;
   uint32_t *hist = (uint32_t *)fixed;
   if (!hist) {
     HIP_TRY(hipMallocAsync(scratch, sort_scratch_bytes(nq), s), "query sort scratch");
@@ -784,22 +831,27 @@ static mknn_status run_query(const mknn_cloud *c, const float *d_q, int64_t nq, 
   a.cnt_entries = d_ce;
   a.cnt_lists = d_cl;
   a.cnt_inserts = d_ci;
+  const bool exact = (d_k == nullptr);
+  const bool wave = !force && !d_ce && use_wave(kmax, exact, nq);
   void *scratch = nullptr;
   float4 *qs = nullptr;
-  mknn_status st = prepare_queries(c, d_q, nq, s, &qs, &scratch, fixed_scratch);
+  mknn_status st = prepare_queries(c, d_q, nq, s,
+                                   wave ? wave_sort_min(kmax, d_plane != nullptr) : kSortMinQueries,
+                                   &qs, &scratch, fixed_scratch);
   if (st != MKNN_OK) return st;
   a.qs = qs;
-  const bool exact = (d_k == nullptr);
   TuneConfig cfg = force ? *force : config_for(kmax, exact, c->dev_n);
   if (lazy) {
-    cfg.family = 3;   // only the row kernels filter marked ranks
+    cfg.family = 3;   // of the tuned kernels only the rows filter marked ranks
     cfg.per_wave = 4;
   }
   a.merge_min = cfg.merge_min;
   // the allocation-free entry point records no timing events (they are created on demand)
   hipError_t e = fixed_scratch ? hipSuccess : timing_mark(s, true);
   if (e == hipSuccess) {
-    if (cfg.family == 1)
+    if (wave)
+      e = dispatch_wave(a, kmax, s);
+    else if (cfg.family == 1)
       e = d_ce ? dispatch_lane<true>(a, kmax, exact, s) : dispatch_lane<false>(a, kmax, exact, s);
     else if (cfg.family == 3 && !d_ce)
       e = dispatch_rows(a, kmax, exact, cfg.per_wave, s);
@@ -1101,7 +1153,7 @@ mknn_status mknn_knn_layout(const mknn_cloud *c, int32_t layout, const float *d_
   a.sz = sz;
   void *scratch = nullptr;
   float4 *qs = nullptr;
-  st = prepare_queries(c, d_q, nq, s, &qs, &scratch);
+  st = prepare_queries(c, d_q, nq, s, kSortMinQueries, &qs, &scratch);
   if (st != MKNN_OK) {
     (void)hipFreeAsync(buf, s);
     return st;
@@ -1280,7 +1332,7 @@ mknn_status mknn_autotune(const mknn_cloud *c, const float *d_q, int64_t nq, int
   // The built-in configuration stays unless a candidate is faster by more than 1%, so that
   // timing noise (a profiler attached, another process on the device) does not flip the
   // choice between near-equal candidates.
-  const TuneConfig def = default_config(S);
+  const TuneConfig def = kDefaultConfig;
   for (size_t t = 0; t < cand.size(); ++t)
     if (cand[t].family == def.family && cand[t].merge_min == def.merge_min &&
         cand[t].per_wave == def.per_wave && ms[t] <= 1.01f * ms[bi]) {

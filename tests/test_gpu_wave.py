@@ -1,0 +1,73 @@
+"""GPU parity of the wave kernel (descents side by side, expansions one query per wavefront) at
+the edges of its layout: queries per wavefront, lanes per query, positions of N."""
+import numpy as np
+import pytest
+
+from tests._compare import compare_rows
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import oracle
+    oracle.build(force=False)
+    from paper_2605_02224_amd import api as A
+    from paper_2605_02224_amd import workloads as W
+    c = W.random_cloud(4000, seed=5, shape="torus")
+    return torch, oracle, A, W, c.by_rank, A.Cloud.build(c.by_rank).upload()
+
+
+def _rows(torch, cl, Q, k, m=None):
+    idx, dist = cl.knn(torch.from_numpy(Q).cuda(), k, m)
+    torch.cuda.synchronize()
+    return idx.cpu().numpy(), dist.cpu().numpy()
+
+
+@pytest.mark.parametrize("k", [1, 2, 15, 16, 17, 31, 32, 33, 63, 64])
+@pytest.mark.parametrize("nq", [1, 3, 5, 8195])
+def test_rows_at_layout_edges(env, k, nq):
+    """Ranks equal the FP64 brute force's (near-ties excused), distances its float32."""
+    torch, oracle, A, W, P, cl = env
+    lo, hi = W.bbox_expanded(P, 1.1)
+    Q = W.uniform_in_box(np.random.default_rng(10 * k + nq), nq, lo, hi)
+    for m in (None, k, 500):
+        idx, dist = _rows(torch, cl, Q, k, m)
+        ri, _, rD = oracle.knn_bruteforce(P, Q, k + 1, m)
+        assert compare_rows(idx, dist, ri[:, :k], rD[:, :k], rD[:, k], P=P, Q=Q, m=m) <= 2
+
+
+@pytest.mark.parametrize("k", [8, 16, 32, 64])
+def test_equal_distances(env, k):
+    """A lattice: whole shells of sites at one distance, ranked by age, exactly."""
+    torch, oracle, A, W, _, _ = env
+    rng = np.random.default_rng(k)
+    g = np.stack(np.meshgrid(*[np.arange(12)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    P = g[rng.permutation(len(g))].astype(np.float32)
+    cl = A.Cloud.build(P).upload()
+    Q = np.concatenate([P[:300], P[:300] + np.float32(0.5)])
+    idx, _ = _rows(torch, cl, Q, k)
+    D = ((Q[:, None, :].astype(np.float64) - P[None].astype(np.float64)) ** 2).sum(-1)
+    assert np.array_equal(idx, np.argsort(D, axis=1, kind="stable")[:, :k])
+
+
+def test_distances_not_finite(env):
+    """NaN and infinite coordinates, and distances past the float32 range: the same rows as
+    the row kernel's order (D, age) gives; other queries of the wavefront are not disturbed."""
+    torch, oracle, A, W, P, cl = env
+    lo, hi = W.bbox_expanded(P, 1.1)
+    Q = W.uniform_in_box(np.random.default_rng(1), 64, lo, hi)
+    want = _rows(torch, cl, Q, 16)[0]
+    B = Q.copy()
+    B[3] = np.nan
+    B[9, 0] = np.inf
+    B[17, 1] = 1e30
+    idx, dist = _rows(torch, cl, B, 16)
+    keep = [i for i in range(64) if i not in (3, 9, 17)]
+    assert np.array_equal(idx[keep], want[keep])
+    assert idx[9].tolist() == list(range(16)) and np.isinf(dist[9]).all()
+    D = ((B[17].astype(np.float64) - P.astype(np.float64)) ** 2).sum(-1)
+    assert np.array_equal(idx[17], np.argsort(D, kind="stable")[:16])
