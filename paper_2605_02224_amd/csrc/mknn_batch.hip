@@ -306,6 +306,8 @@ void knn_batch_flat_kernel(const BatchHeader *h, const QueryArgs *reqs, const Ba
   while (__ballot(w.phase == kRowDescent) != 0)
     w.step_descent(a, a.ent, a.lst, l, g, a.k, m, a.merge_min);
   w.settle(a, l, a.k);
+  if constexpr (S == 1)
+    if (gather_rows(a.k, 4 * nw)) w.expand_all(a, a.ent, a.lst, l, g, a.k, m);
   while (__ballot(w.phase != kRowIdle) != 0)
     w.step_expand(a, a.ent, a.lst, a.merge_min, l, g, a.k, m);
 }

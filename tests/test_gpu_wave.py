@@ -71,3 +71,44 @@ def test_distances_not_finite(env):
     assert idx[9].tolist() == list(range(16)) and np.isinf(dist[9]).all()
     D = ((B[17].astype(np.float64) - P.astype(np.float64)) ** 2).sum(-1)
     assert np.array_equal(idx[17], np.argsort(D, kind="stable")[:16])
+
+
+def _chunks(torch, q, f, size=50000):
+    parts = [f(q[i:i + size].contiguous()) for i in range(0, q.shape[0], size)]
+    torch.cuda.synchronize()
+    return torch.cat([p[0] for p in parts]), torch.cat([p[1] for p in parts])
+
+
+def _lattice(A, side, seed):
+    g = np.stack(np.meshgrid(*[np.arange(side)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    P = g[np.random.default_rng(seed).permutation(len(g))].astype(np.float32)
+    return P, A.Cloud.build(P).upload()
+
+
+@pytest.mark.parametrize("k", [9, 12, 16])
+@pytest.mark.parametrize("shape", ["torus", "lattice"])
+def test_gathered_rows(env, k, shape):
+    """Launches and batches large enough that rows gather their candidates (k > 8) against the
+    same queries in small launches: the same ranks and distances, NaN and infinities included."""
+    torch, oracle, A, W, P, cl = env
+    if shape == "lattice":
+        P, cl = _lattice(A, 15, k)
+    rng = np.random.default_rng(k)
+    lo, hi = W.bbox_expanded(P, 1.1)
+    Q = W.uniform_in_box(rng, 196608, lo, hi)
+    if shape == "lattice":
+        Q = np.round(2 * Q).astype(np.float32) / 2
+    Q[5, 0], Q[77, 2] = np.inf, 1e30
+    q = torch.from_numpy(Q).cuda()
+    for m in (None, 300):
+        idx, dist = cl.knn(q, k, m)
+        ri, rd = _chunks(torch, q, lambda c: cl.knn(c, k, m))
+        assert torch.equal(idx, ri) and torch.equal(dist, rd)
+    items = A.alloc_outputs([(cl, q, k, None), (cl, q[:100].contiguous(), k, None)])
+    plan = A.BatchPlan(len(items), sum(it[1].shape[0] for it in items))
+    plan.run(items)
+    torch.cuda.synchronize()
+    ri, rd = _chunks(torch, q, lambda c: cl.knn(c, k))
+    assert torch.equal(items[0][4], ri) and torch.equal(items[0][5], rd)
+    assert torch.equal(items[1][4], ri[:100])
+    plan.close()
