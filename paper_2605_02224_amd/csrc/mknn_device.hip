@@ -2,14 +2,15 @@
 // the query kernels and their launch configuration (with the autotuner's table), list
 // deltas for deletion and insertion, and the plane fit.
 //
-// Four kernel families compute the same rows (the 1-NN descent of Alg. 1, the k-expansion
+// Five kernel families compute the same rows (the 1-NN descent of Alg. 1, the k-expansion
 // of Alg. 2, the prefix bound of Sec. 4.2), with identical float64 keys (D, rank):
 //   lane  (knn_lane_kernel, below): one query per lane, N a register-resident sorted array;
 //   group (knn_group.h): 16 lanes per query, the four rows of a wavefront in lockstep phases
 //         (it also carries the work-counting variant);
 //   rows  (knn_rows.h): 16 lanes per query, rows scheduled independently;
 //   wave  (knn_wave.h): descents side by side, expansions one query per wavefront.
-// use_wave() chooses between the last two.
+//   scan  (knn_scan.h): the wave kernel's descents, four lists of a query scanned by rows.
+// walk_for() chooses between the last three.
 // In the lane kernel every examined entry, transition sites included, is offered to N;
 // offering more true sites than Alg. 1 does never changes the result, and it lets the
 // final, completely scanned list of the descent serve as Alg. 2's first iteration.
@@ -31,6 +32,7 @@
 #include "device_common.h"
 #include "knn_group.h"
 #include "knn_rows.h"
+#include "knn_scan.h"
 #include "knn_wave.h"
 #include "planefit.h"
 
@@ -214,8 +216,8 @@ constexpr int kScanBlock = 1024;
 constexpr int kScanBlocks = kMortonBins / kScanBlock;
 static_assert(kScanBlocks <= 1024, "one workgroup scans the block totals");
 constexpr int64_t kSortMinQueries = 8192;
-// Up to this many queries the wave kernel is the faster one at every k (see use_wave()).
-constexpr int64_t kLargeQueries = 65536;
+// Sizes between which walk_for() chooses.
+constexpr int64_t kSmallQueries = 16384, kLargeQueries = 65536;
 // The wave kernel gains less from neighbours in a wavefront than the bucketing costs (five
 // launches, 20 us and up) until launches are larger: 1M-point torus, k = 16, 65536 queries 182
 // us as they come, 215 us bucketed; 262144 queries 594 and 590; 1000000 queries 2081 and 1928.
@@ -576,8 +578,7 @@ hipError_t timing_mark(hipStream_t s, bool start) {
 // candidates per chunk from which k <= 16 merges with the network instead of inserting one
 // by one, and the queries per wavefront of the row kernel.  mknn_autotune fills a table
 // keyed by (device, slots per lane S, k == 16 S, log2 n); launches look their key up and
-// fall back to the measured defaults, but for those that the wave kernel takes for their
-// size.  Environment variables override all of it (experiments).
+// fall back to the measured defaults, but for those that the wave and scan kernels take.  Environment variables override all of it (experiments).
 // ---------------------------------------------------------------------------------------
 static long env_long(const char *name, long dflt) {
   const char *e = getenv(name);
@@ -598,12 +599,28 @@ constexpr TuneConfig kDefaultConfig = {3, 8, 4};
 //   98304      101 / 81    182 / 200    255 / 268    328 / 305    433 / 407    899 / 708
 //   262144     213 / 172   397 / 430    567 / 590    730 / 676    990 / 917   2071 / 1591
 //   1000000    695 / 534  1388 / 1433  1947 / 1928  2507 / 2199  3373 / 2974  7195 / 5374
-// With a k and prefix per query many lists end early in their prefix and leave the wave
-// kernel's batches half empty: 300k queries of k <= 12, rows 1.70 ms, wave 1.78 ms.
-static bool use_wave(int kmax, bool exact, int64_t nq) {
+// Prefixes cut lists short, which leaves the wave kernel's batches half empty; the scan kernel
+// drops a list where the prefix ends, and the rows lose least.  Over 400k points, rows / wave /
+// scan, prefix of 100k: 65536 queries k=8 114 / 145 / 133, k=32 268 / 352 / 297, k=64 579 / 720 /
+// 576; 500k queries k=16 680 / 1139 / 866, k=20 1067 / 1337 / 986, k=64 3622 / 3724 / 2447; 20000
+// queries k=32 131 / 148 / 206; 4096 queries k=16 50 / 39 / 52.  A k and prefix per query
+// (prefixes of 400 to 400k; all 400k): 20000 queries k <= 32 236 / 207 / 207 (250 / 184 / 218);
+// 131072 queries k <= 16 390 / 372 / 346 (409 / 338 / 389); 500k queries k <= 16 878 / 983 / 890
+// (944 / 871 / 965), k <= 32 1414 / 1418 / 1147 (1464 / 1145 / 1243).
+enum class Walk { kRows, kWaves, kScan };
+static Walk walk_for(int kmax, bool uniform, bool prefix, int64_t nq) {
   static const char *const v = getenv("MKNN_KERNEL");
-  if (v) return v[0] == 'w';
-  return nq <= kLargeQueries || (exact && (kmax == 1 || kmax > 16));
+  if (v) return v[0] == 'w' ? Walk::kWaves : v[0] == 's' ? Walk::kScan : Walk::kRows;
+  if (nq <= kSmallQueries || (uniform && kmax == 1)) return Walk::kWaves;
+  if (!uniform) {
+    if (nq <= kLargeQueries) return Walk::kWaves;
+    return kmax <= 16 && nq > kWaveSortQueries ? Walk::kRows : Walk::kScan;
+  }
+  if (prefix) {
+    const int64_t scan_min = kmax > 32 ? kLargeQueries : kWaveSortQueries;
+    return kmax > 16 && nq >= scan_min ? Walk::kScan : Walk::kRows;
+  }
+  return nq <= kLargeQueries || kmax > 16 ? Walk::kWaves : Walk::kRows;
 }
 
 static std::mutex g_tune_mu;
@@ -742,20 +759,25 @@ static hipError_t dispatch_rows(const QueryArgs &a, int kmax, bool exact, int32_
 }
 
 template <int DW, int R>
-static hipError_t launch_wave(const QueryArgs &a, int32_t per_wave, hipStream_t s) {
+static hipError_t launch_wave(const QueryArgs &a, int32_t per_wave, bool scan, hipStream_t s) {
   const int64_t waves = (a.nq + per_wave - 1) / per_wave;
   const uint32_t blocks = (uint32_t)((waves + 3) / 4);
-  hipLaunchKernelGGL((knn_wave_kernel<DW, R>), dim3(blocks), dim3(256), 0, s, a, per_wave);
+  if (scan)
+    hipLaunchKernelGGL((knn_scan_kernel<DW, R>), dim3(blocks), dim3(256), 0, s, a, per_wave);
+  else
+    hipLaunchKernelGGL((knn_wave_kernel<DW, R>), dim3(blocks), dim3(256), 0, s, a, per_wave);
   return hipGetLastError();
 }
 
-static hipError_t dispatch_wave(const QueryArgs &a, int kmax, hipStream_t s) {
+static hipError_t dispatch_wave(const QueryArgs &a, int kmax, bool scan, hipStream_t s) {
   const WaveShape w = wave_shape(a.nq, kmax);
   if (kmax <= 16)
-    return w.lanes == 8 ? launch_wave<8, 16>(a, w.per_wave, s) : launch_wave<16, 16>(a, w.per_wave, s);
+    return w.lanes == 8 ? launch_wave<8, 16>(a, w.per_wave, scan, s)
+                        : launch_wave<16, 16>(a, w.per_wave, scan, s);
   if (kmax <= 32)
-    return w.lanes == 8 ? launch_wave<8, 32>(a, w.per_wave, s) : launch_wave<16, 32>(a, w.per_wave, s);
-  return launch_wave<16, 64>(a, w.per_wave, s);
+    return w.lanes == 8 ? launch_wave<8, 32>(a, w.per_wave, scan, s)
+                        : launch_wave<16, 32>(a, w.per_wave, scan, s);
+  return launch_wave<16, 64>(a, w.per_wave, scan, s);
 }
 
 // Bytes of scratch the Morton bucketing of nq queries may need (0 below every sort threshold).
@@ -832,11 +854,13 @@ static mknn_status run_query(const mknn_cloud *c, const float *d_q, int64_t nq, 
   a.cnt_lists = d_cl;
   a.cnt_inserts = d_ci;
   const bool exact = (d_k == nullptr);
-  const bool wave = !force && !d_ce && use_wave(kmax, exact, nq);
+  const Walk walk =
+      force || d_ce ? Walk::kRows : walk_for(kmax, exact, exact && m < c->dev_n, nq);
   void *scratch = nullptr;
   float4 *qs = nullptr;
   mknn_status st = prepare_queries(c, d_q, nq, s,
-                                   wave ? wave_sort_min(kmax, d_plane != nullptr) : kSortMinQueries,
+                                   walk == Walk::kRows ? kSortMinQueries
+                                                       : wave_sort_min(kmax, d_plane != nullptr),
                                    &qs, &scratch, fixed_scratch);
   if (st != MKNN_OK) return st;
   a.qs = qs;
@@ -849,8 +873,8 @@ static mknn_status run_query(const mknn_cloud *c, const float *d_q, int64_t nq, 
   // the allocation-free entry point records no timing events (they are created on demand)
   hipError_t e = fixed_scratch ? hipSuccess : timing_mark(s, true);
   if (e == hipSuccess) {
-    if (wave)
-      e = dispatch_wave(a, kmax, s);
+    if (walk != Walk::kRows)
+      e = dispatch_wave(a, kmax, walk == Walk::kScan, s);
     else if (cfg.family == 1)
       e = d_ce ? dispatch_lane<true>(a, kmax, exact, s) : dispatch_lane<false>(a, kmax, exact, s);
     else if (cfg.family == 3 && !d_ce)

@@ -112,3 +112,36 @@ def test_gathered_rows(env, k, shape):
     assert torch.equal(items[0][4], ri) and torch.equal(items[0][5], rd)
     assert torch.equal(items[1][4], ri[:100])
     plan.close()
+
+
+@pytest.mark.parametrize("kmax", [2, 16, 17, 32, 64])
+@pytest.mark.parametrize("shape", ["torus", "lattice"])
+def test_scanned_lists(env, kmax, shape):
+    """Large launches that scan lists by rows (a k and prefix per query; prefixes with long
+    rows) against the same queries in small launches."""
+    torch, oracle, A, W, P, cl = env
+    if shape == "lattice":
+        P, cl = _lattice(A, 15, kmax)
+    rng = np.random.default_rng(kmax)
+    lo, hi = W.bbox_expanded(P, 1.1)
+    Q = W.uniform_in_box(rng, 65537, lo, hi)
+    if shape == "lattice":
+        Q = np.round(2 * Q).astype(np.float32) / 2
+    Q[5, 0], Q[77, 2] = np.inf, 1e30
+    q = torch.from_numpy(Q).cuda()
+    kq = torch.from_numpy(rng.integers(1, kmax + 1, len(Q)).astype(np.int32)).cuda()
+    kq[:200] = kmax
+    mq = torch.from_numpy(np.exp(rng.uniform(0, np.log(len(P)), len(Q))).astype(np.int32)).cuda()
+    mq = mq.clamp(1, len(P))
+    got = cl.knn_var(q, kq, mq)
+    parts = []
+    for i in range(0, len(Q), 16000):
+        parts.append(cl.knn_var(q[i:i + 16000].contiguous(), kq[i:i + 16000].contiguous(),
+                                mq[i:i + 16000].contiguous()))
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], torch.cat([p[0] for p in parts]))
+    assert torch.equal(got[1], torch.cat([p[1] for p in parts]))
+    for m in (1, kmax, 600):
+        idx, dist = cl.knn(q, kmax, m)
+        ri, rd = _chunks(torch, q, lambda c: cl.knn(c, kmax, m), 16000)
+        assert torch.equal(idx, ri) and torch.equal(dist, rd)
