@@ -145,3 +145,22 @@ def test_scanned_lists(env, kmax, shape):
         idx, dist = cl.knn(q, kmax, m)
         ri, rd = _chunks(torch, q, lambda c: cl.knn(c, kmax, m), 16000)
         assert torch.equal(idx, ri) and torch.equal(dist, rd)
+
+
+@pytest.mark.parametrize("n", [1, 2, 4, 5, 17, 300, 4097])
+def test_arena_gathered_on_device(env, n):
+    """The records an upload gathers on the device against the image packed on the host
+    (compact), and both against the brute force."""
+    torch, oracle, A, W, _, _ = env
+    rng = np.random.default_rng(n)
+    P = rng.standard_normal((n, 3)).astype(np.float32)
+    cl = A.Cloud.build(P).upload()
+    Q = rng.standard_normal((130, 3)).astype(np.float32)
+    a = _rows(torch, cl, Q, 8)
+    cl.compact()
+    b = _rows(torch, cl, Q, 8)
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+    D = ((Q[:, None, :].astype(np.float64) - P[None].astype(np.float64)) ** 2).sum(-1)
+    k = min(8, n)
+    assert np.array_equal(a[0][:, :k], np.argsort(D, axis=1, kind="stable")[:, :k])
+    assert (a[0][:, k:] == -1).all()
