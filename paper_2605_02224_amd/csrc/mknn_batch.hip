@@ -47,6 +47,7 @@
 #include "device_common.h"
 #include "knn_group.h"
 #include "knn_rows.h"
+#include "knn_wave.h"
 
 namespace mknn {
 
@@ -67,6 +68,7 @@ struct BatchHeader {
   int32_t sorted;
   int64_t total_q;
   int64_t fwaves[kClasses];                // flat launch: wavefronts of work per class
+  int32_t by_wave[kClasses];               // flat launch: the class goes by the wave kernel
   int32_t qbound[kClasses][kQueues + 1];   // entry index ranges per (class, queue)
   int32_t qtiles[kClasses][kQueues];       // tiles per (class, queue)
   int32_t tile[kClasses];                  // queries per tile, per class
@@ -266,6 +268,35 @@ void knn_batch_rows_kernel(const BatchHeader *h, const QueryArgs *reqs, const Ba
   }
 }
 
+// The request and its four queries that a wavefront of class `cls` takes.
+struct FlatWork {
+  const QueryArgs *req = nullptr;   // NULL: nothing to do
+  int64_t begin = 0, end = 0, waves = 0;
+};
+__device__ __forceinline__ FlatWork flat_work(const BatchHeader *h, const QueryArgs *reqs,
+                                              const BatchEntry *ents, const int64_t *woff, int cls) {
+  FlatWork w;
+  const int64_t nw = h->fwaves[cls];
+  const int64_t need = (nw + 3) >> 2;              // workgroups of four wavefronts
+  const int64_t per = (need + 7) >> 3;
+  const int64_t i = blockIdx.x >> 3, x = blockIdx.x & 7;
+  if (i >= per) return w;
+  const int64_t wg = x * per + i;
+  const int64_t wave = __builtin_amdgcn_readfirstlane((int32_t)(4 * wg + (threadIdx.x >> 6)));
+  if (wg >= need || wave >= nw) return w;        // whole wavefronts leave
+  // the entry owning this wavefront: the last one whose first wavefront is <= wave
+  int32_t lo = h->qbound[cls][0], hi = h->qbound[cls][kQueues];
+  while (hi - lo > 1) {
+    const int32_t mid = (lo + hi) >> 1;
+    if (woff[mid] <= wave) lo = mid; else hi = mid;
+  }
+  w.req = reqs + __builtin_amdgcn_readfirstlane(ents[lo].req);
+  w.begin = 4 * (wave - woff[lo]);
+  w.end = w.begin + 4 < w.req->nq ? w.begin + 4 : w.req->nq;
+  w.waves = nw;
+  return w;
+}
+
 // Flat batched kernel: the plain launch over the concatenated batch.  Class `cls`'s
 // requests (queue entries qbound[cls][0] .. qbound[cls][kQueues]) are laid end to end,
 // request e taking wavefronts woff[e] .. woff[e] + ceil(nq / 4) - 1, each four consecutive
@@ -280,36 +311,42 @@ template <int S, bool LAZY = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAZY ? (S == 1 ? 8 : 1) : 8, 8)))
 void knn_batch_flat_kernel(const BatchHeader *h, const QueryArgs *reqs, const BatchEntry *ents,
                            const int64_t *woff, int cls) {
-  const int64_t nw = h->fwaves[cls];
-  const int64_t need = (nw + 3) >> 2;              // workgroups of four wavefronts
-  const int64_t per = (need + 7) >> 3;
-  const int64_t i = blockIdx.x >> 3, x = blockIdx.x & 7;
-  if (i >= per) return;
-  const int64_t wg = x * per + i;
-  const int64_t wave = __builtin_amdgcn_readfirstlane((int32_t)(4 * wg + (threadIdx.x >> 6)));
-  if (wg >= need || wave >= nw) return;          // whole wavefronts leave
-  // the entry owning this wavefront: the last one whose first wavefront is <= wave
-  int32_t lo = h->qbound[cls][0], hi = h->qbound[cls][kQueues];
-  while (hi - lo > 1) {
-    const int32_t mid = (lo + hi) >> 1;
-    if (woff[mid] <= wave) lo = mid; else hi = mid;
-  }
-  const int32_t req = __builtin_amdgcn_readfirstlane(ents[lo].req);
-  const QueryArgs a = reqs[req];
-  const int64_t begin = 4 * (wave - woff[lo]);
-  const int64_t end = begin + 4 < a.nq ? begin + 4 : a.nq;
+  if (S > 1 && h->by_wave[cls]) return;
+  const FlatWork f = flat_work(h, reqs, ents, woff, cls);
+  if (!f.req) return;
+  const QueryArgs a = *f.req;
   const int lane = threadIdx.x & 63, l = lane & 15, g = lane >> 4;
   const int32_t m = (int32_t)(a.m < a.n ? (int64_t)a.m : a.n);
   RowWalker<S, false, (S == 1), true, LAZY> w;
   w.N.init();
-  if (begin + g < end) w.begin(a, begin + g, l);
+  if (f.begin + g < f.end) w.begin(a, f.begin + g, l);
   while (__ballot(w.phase == kRowDescent) != 0)
     w.step_descent(a, a.ent, a.lst, l, g, a.k, m, a.merge_min);
   w.settle(a, l, a.k);
   if constexpr (S == 1)
-    if (gather_rows(a.k, 4 * nw)) w.expand_all(a, a.ent, a.lst, l, g, a.k, m);
+    if (gather_rows(a.k, 4 * f.waves)) w.expand_all(a, a.ent, a.lst, l, g, a.k, m);
   while (__ballot(w.phase != kRowIdle) != 0)
     w.step_expand(a, a.ent, a.lst, a.merge_min, l, g, a.k, m);
+}
+
+// The same launch by the wave kernel's walk, for classes of k > 16 whose requests all search
+// their whole cloud: four descents side by side, then the four expansions.  8 requests over
+// clouds of 20k points, rows / waves, ms: k = 64, 65536 queries each 4.04 / 2.70, 256 each 0.202
+// / 0.175; k = 32 1.64 / 1.42 and 0.107 / 0.094; k = 20 1.12 / 1.01 and 0.083 / 0.077.  In
+// prefixes its batches of lists run half empty (see walk_for()): those classes go by rows.
+template <int S>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8)))
+void knn_batch_wave_kernel(const BatchHeader *h, const QueryArgs *reqs, const BatchEntry *ents,
+                           const int64_t *woff, int cls) {
+  static_assert(S > 1, "classes of k > 16");
+  constexpr int R = S == 2 ? 32 : 64;
+  __shared__ WaveLds<16, R> lds[4];
+  if (!h->by_wave[cls]) return;
+  const FlatWork f = flat_work(h, reqs, ents, woff, cls);
+  if (!f.req || f.begin >= f.end) return;
+  const QueryArgs a = *f.req;
+  wave_walk<16, R>(a, lds[__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))], f.begin,
+                   (int)(f.end - f.begin));
 }
 
 // The persistent tile-claiming kernel instead of the flat one (MKNN_BATCH_PERSISTENT=1 in
@@ -364,7 +401,8 @@ struct mknn_batch_plan {
   uint32_t *h_overflow = nullptr;   // pinned: per request, rows a run could not certify
   bool lazy_run = false;            // the last run filtered pending deletions
   int32_t merge_min[kClasses] = {0, 0, 0, 0};   // per class (S - 1); 0 = the autotuner's table
-  uint32_t classes = 0xF;           // register classes that plan_enqueue launches (bit S-1)
+  // register classes that plan_enqueue launches: bit S-1 by rows, bit S+3 by waves
+  uint32_t classes = 0xF;
   uint32_t graph_classes[2] = {0, 0};   // the classes each captured graph launches
   uint32_t grid_stream = 1;
 };
@@ -416,6 +454,12 @@ static void launch_batch_kernels(const mknn_batch_plan *p, hipStream_t s, const 
       hipLaunchKernelGGL((knn_batch_flat_kernel<3, LAZY>), gf, dim3(256), 0, s, hdr, reqs, ents, woff, 2);
     if (c4)
       hipLaunchKernelGGL((knn_batch_flat_kernel<4, LAZY>), gf, dim3(256), 0, s, hdr, reqs, ents, woff, 3);
+    if (p->classes & 0x20u)
+      hipLaunchKernelGGL((knn_batch_wave_kernel<2>), gf, dim3(256), 0, s, hdr, reqs, ents, woff, 1);
+    if (p->classes & 0x40u)
+      hipLaunchKernelGGL((knn_batch_wave_kernel<3>), gf, dim3(256), 0, s, hdr, reqs, ents, woff, 2);
+    if (p->classes & 0x80u)
+      hipLaunchKernelGGL((knn_batch_wave_kernel<4>), gf, dim3(256), 0, s, hdr, reqs, ents, woff, 3);
   }
 }
 
@@ -607,9 +651,13 @@ static mknn_status plan_run(mknn_batch_plan *p, const mknn_request *reqs, int32_
   }
   for (int32_t r = 0; r <= nreq; ++r) d_qoff[r] = qoff[r];
   // ---- run (graph replay or eager)
+  // classes of more than 16 neighbours whose requests all search their whole cloud
+  for (int c = 0; c < kClasses; ++c) hdr->by_wave[c] = c > 0 && !p->persistent;
+  for (int32_t r = 0; r < nreq; ++r)
+    if (args[r].m < args[r].n && reqs[r].nq > 0) hdr->by_wave[cls[r]] = 0;
   uint32_t need = 0;   // the classes with work in this batch
   for (int c = 0; c < kClasses; ++c)
-    if (class_q[c] > 0) need |= 1u << c;
+    if (class_q[c] > 0) need |= 1u << (hdr->by_wave[c] ? c + 4 : c);
   if (p->use_graph && !timing_enabled()) {
     const int v = any_lazy ? 1 : 0;
     if (p->exec[v] && (need & ~p->graph_classes[v])) {

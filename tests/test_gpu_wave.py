@@ -164,3 +164,24 @@ def test_arena_gathered_on_device(env, n):
     k = min(8, n)
     assert np.array_equal(a[0][:, :k], np.argsort(D, axis=1, kind="stable")[:, :k])
     assert (a[0][:, k:] == -1).all()
+
+
+@pytest.mark.parametrize("nq", [1, 5, 203])
+def test_batch_classes_by_rows_and_waves(env, nq):
+    """One plan, run with whole clouds (classes of k > 16 by waves), prefixes (by rows), both in
+    one class, and whole clouds again (the same graph): always the plain launch's rows."""
+    torch, oracle, A, W, P, cl = env
+    rng = np.random.default_rng(nq)
+    lo, hi = W.bbox_expanded(P, 1.1)
+    plan = A.BatchPlan(8, 8 * 203)
+    for ms in ((None,) * 5, (900,) * 5, (None, 900, None, 900, None), (None,) * 5):
+        reqs = [(cl, torch.from_numpy(W.uniform_in_box(rng, nq + i, lo, hi)).cuda(), k, m)
+                for i, (k, m) in enumerate(zip((10, 17, 32, 33, 64), ms))]
+        items = A.alloc_outputs([r[:3] + (cl.n if r[3] is None else r[3],) for r in reqs])
+        plan.run(items)
+        torch.cuda.synchronize()
+        for (_, q, k, m), it in zip(reqs, items):
+            ri, rd = cl.knn(q, k, m)
+            torch.cuda.synchronize()
+            assert torch.equal(it[4], ri) and torch.equal(it[5], rd)
+    plan.close()
