@@ -271,7 +271,7 @@ void knn_batch_rows_kernel(const BatchHeader *h, const QueryArgs *reqs, const Ba
 // The request and its four queries that a wavefront of class `cls` takes.
 struct FlatWork {
   const QueryArgs *req = nullptr;   // NULL: nothing to do
-  int64_t begin = 0, end = 0, waves = 0;
+  int64_t begin = 0, waves = 0;
 };
 __device__ __forceinline__ FlatWork flat_work(const BatchHeader *h, const QueryArgs *reqs,
                                               const BatchEntry *ents, const int64_t *woff, int cls) {
@@ -292,7 +292,6 @@ __device__ __forceinline__ FlatWork flat_work(const BatchHeader *h, const QueryA
   }
   w.req = reqs + __builtin_amdgcn_readfirstlane(ents[lo].req);
   w.begin = 4 * (wave - woff[lo]);
-  w.end = w.begin + 4 < w.req->nq ? w.begin + 4 : w.req->nq;
   w.waves = nw;
   return w;
 }
@@ -315,11 +314,12 @@ void knn_batch_flat_kernel(const BatchHeader *h, const QueryArgs *reqs, const Ba
   const FlatWork f = flat_work(h, reqs, ents, woff, cls);
   if (!f.req) return;
   const QueryArgs a = *f.req;
+  const int64_t end = f.begin + 4 < a.nq ? f.begin + 4 : a.nq;
   const int lane = threadIdx.x & 63, l = lane & 15, g = lane >> 4;
   const int32_t m = (int32_t)(a.m < a.n ? (int64_t)a.m : a.n);
   RowWalker<S, false, (S == 1), true, LAZY> w;
   w.N.init();
-  if (f.begin + g < f.end) w.begin(a, f.begin + g, l);
+  if (f.begin + g < end) w.begin(a, f.begin + g, l);
   while (__ballot(w.phase == kRowDescent) != 0)
     w.step_descent(a, a.ent, a.lst, l, g, a.k, m, a.merge_min);
   w.settle(a, l, a.k);
@@ -343,10 +343,12 @@ void knn_batch_wave_kernel(const BatchHeader *h, const QueryArgs *reqs, const Ba
   __shared__ WaveLds<16, R> lds[4];
   if (!h->by_wave[cls]) return;
   const FlatWork f = flat_work(h, reqs, ents, woff, cls);
-  if (!f.req || f.begin >= f.end) return;
+  if (!f.req) return;
   const QueryArgs a = *f.req;
+  const int64_t end = f.begin + 4 < a.nq ? f.begin + 4 : a.nq;
+  if (f.begin >= end) return;
   wave_walk<16, R>(a, lds[__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))], f.begin,
-                   (int)(f.end - f.begin));
+                   (int)(end - f.begin));
 }
 
 // The persistent tile-claiming kernel instead of the flat one (MKNN_BATCH_PERSISTENT=1 in
