@@ -473,10 +473,12 @@ __device__ __forceinline__ bool expand(const QueryArgs &a, WaveLds<DW, R> &w, co
     // ---- insert
     uint32_t lost = kPadKey;   // keys that fall out of the lanes
     if (nc <= kWaveInsert) {
-      // one by one: every position keeps the middle of its key, the one before and the new
+      // one by one: every position keeps the middle of its key, the one before and the new.
+      // The last lane may fill up within these keys, so each may push one out (an empty
+      // lane's key is above every threshold)
       do {
         const uint32_t nk = readlane_u32(key, pop_lane(fresh));
-        if (nreal == 64) lost = min(lost, max(readlane_u32(N, 63), nk));
+        lost = min(lost, max(readlane_u32(N, 63), nk));
         N = median(wave_shr1(N), nk, N);
       } while (fresh);
     } else {

@@ -185,3 +185,48 @@ def test_batch_classes_by_rows_and_waves(env, nq):
             torch.cuda.synchronize()
             assert torch.equal(it[4], ri) and torch.equal(it[5], rd)
     plan.close()
+
+
+def _exact_rows(P, Q, k, m, live=None):
+    """Ranks of the k nearest of the first m points by (D, age), float64."""
+    d = Q[:, None, :].astype(np.float64) - P[None, :m].astype(np.float64)
+    D = d[..., 0] * d[..., 0] + d[..., 1] * d[..., 1] + d[..., 2] * d[..., 2]
+    if live is not None:
+        D[:, ~live[:m]] = np.inf
+    return np.argsort(D, axis=1, kind="stable")[:, :k]
+
+
+@pytest.mark.parametrize("jitter", [0.0, 1e-5])
+@pytest.mark.parametrize("sites", [64, 65, 66, 68, 72, 80])
+def test_last_position_fills_within_an_insertion(env, sites, jitter):
+    """Little more than 64 sites, whole shells of them at one distance or nearly so: the 64th
+    position fills among a few new keys.  Whole clouds and prefixes, the plain and the batched
+    call, pending deletions that widen the walk to 64; by (D, age) in float64, exactly."""
+    torch, oracle, A, W, _, _ = env
+    rng = np.random.default_rng(1000 * sites + (jitter > 0))
+    g = np.stack(np.meshgrid(*[np.arange(6)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    Q = (rng.integers(-1, 12, (1500, 3)) / 2).astype(np.float32)
+    q = torch.from_numpy(Q).cuda()
+    for n in (sites, 216):
+        P = g[rng.permutation(216)[:n]].astype(np.float32)
+        P = (P + jitter * rng.standard_normal(P.shape)).astype(np.float32)
+        cl = A.Cloud.build(P).upload()
+        items = []
+        for k in (60, 62, 63, 64):
+            idx, _ = _rows(torch, cl, Q, k, sites)
+            assert np.array_equal(idx, _exact_rows(P, Q, k, sites)), (n, k)
+            items.append((cl, q, k, sites))
+        items = A.alloc_outputs(items)
+        plan = A.BatchPlan(len(items), len(items) * len(Q))
+        plan.run(items)
+        torch.cuda.synchronize()
+        for it in items:
+            assert np.array_equal(it[4].cpu().numpy(), _exact_rows(P, Q, it[2], sites)), (n, it[2])
+        plan.close()
+        gone = rng.choice(np.arange(1, sites), 15, replace=False).astype(np.int32)
+        live = np.ones(n, bool)
+        live[gone] = False
+        cl.delete_lazy(gone)
+        k = min(48, sites - 16)
+        idx, _ = _rows(torch, cl, Q, k, sites)
+        assert np.array_equal(idx, _exact_rows(P, Q, k, sites, live)), (n, "pending")
