@@ -51,7 +51,7 @@ HEADLINE_KERNEL = "knn_rows_kernel<1, true, true, true, false>"
 
 # the translation unit of the plain query path and the headers its kernels are built from
 KERNEL_SOURCES = ("mknn_device.hip", "knn_kernels.h", "knn_group.h", "knn_rows.h",
-                  "knn_scan.h", "knn_wave.h",
+                  "knn_scan.h", "knn_wave.h", "launch_rule.h",
                   "device_common.h", "planefit.h")
 
 

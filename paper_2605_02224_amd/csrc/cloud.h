@@ -48,6 +48,7 @@ struct HostPack {
   std::vector<float> pts;          // 4 floats per rank {x, y, z, 0}
   int64_t nnz = 0;                 // records in use
   int64_t cap = 0;                 // records to allocate (slack for later deltas + padding)
+  int64_t longest = 0;             // entries of the longest list
 };
 // List segments rewritten by a deletion batch, ready to be appended to the device arena, or,
 // when the arena's slack would run out, a complete new image of the lists.
@@ -103,6 +104,8 @@ struct mknn_cloud {
   float dev_hxyz[3] = {0, 0, 0};   // its coordinates
   int64_t dev_n = 0;               // ranks the device lists cover
   float dev_lo[3] = {0, 0, 0}, dev_hi[3] = {0, 0, 0};   // bounding box (for query bucketing)
+  int64_t dev_longest = 0;         // entries of the longest list (at most: after updates, until
+                                   // the next pack)
 
   // Pending (lazy) deletions: ranks marked as deleted that the device lists still hold
   // until Alg. 3 is applied to them.  The device array holds, per rank, the epoch of the

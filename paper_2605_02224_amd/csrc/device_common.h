@@ -153,19 +153,6 @@ struct TuneConfig {
   int32_t per_wave;    // family 3: queries per wavefront
 };
 
-// How the wave kernel lays nq queries out: lanes per query in the descent, and queries per
-// wavefront (at most 64 / lanes; a second one only once every resident wavefront has one).
-struct WaveShape {
-  int32_t lanes, per_wave;
-};
-inline WaveShape wave_shape(int64_t nq, int kmax) {
-  const int64_t resident = 32 * (int64_t)device_cus();
-  WaveShape w;
-  w.lanes = kmax <= 32 && nq >= 8 * resident ? 8 : 16;
-  w.per_wave = 1;
-  while (w.per_wave * 2 <= 64 / w.lanes && nq > w.per_wave * resident) w.per_wave *= 2;
-  return w;
-}
 TuneConfig config_for(int kmax, bool exact, int64_t n);
 
 // Optional HIP-event timing of the main query kernels (defined in mknn_device.hip).

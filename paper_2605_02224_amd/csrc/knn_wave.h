@@ -383,56 +383,81 @@ __device__ __forceinline__ bool expand(const QueryArgs &a, WaveLds<DW, R> &w, co
     const uint32_t lim = min(readlane_u32(N, q.k - 2) | kTieBits, kMaxKey);
     const uint64_t open = lanes_where(N <= lim) & ~lanes_where((N & 1u) != 0);
     if (!(open | pend)) break;
-    // descriptors of the next unexpanded sites (about 4 fit a batch)
-    uint64_t dsc = __builtin_nondeterministic_value(dsc), win = 0;
-    if (open) {
-      win = open & (0xffull << __builtin_ctzll(open));
-      if (in_mask(win)) dsc = a.lst[(uint32_t)w.r_of(N)];
-    }
-    const uint32_t dst = (uint32_t)dsc, dlen = (uint32_t)(dsc >> 32);
-    // ---- lay the lists over the lanes.  The i-th list starts at the i-th set bit of
-    //      `starts`; lane i of `at` holds its first entry's index less that lane
-    uint32_t at = __builtin_nondeterministic_value(at), rest = __builtin_nondeterministic_value(rest);
-    uint32_t total = 0;
-    uint64_t starts = 0, cut = 0;
-    int lists = 0;
-    auto lay = [&](uint32_t st, uint32_t len) {
-      at = writelane_u32(st - total, lists, at);
-      ++lists;
-      set_bit(starts, total);
-      const uint32_t room = min(cap, 64u - total);
-      total += min(len, room);
-      if (len > room) {
-        set_bit(cut, total - 1);
-        rest = writelane_u32(len - room, (int)total - 1, rest);
+    uint32_t u;
+    uint64_t cand;
+    const uint64_t runs = pend & lanes_where(plen >= 64);
+    if (runs) {
+      // what is left of a long list is read on by itself, 64 entries a step: neither the
+      // descriptors of the sites behind it are loaded nor a layout made (200k points with 20
+      // far outliers, 53551 entries in the longest list: 300 queries of k=8 1.26 ms, now 0.96;
+      // 65536 of k=20 10.97 ms, now 4.9)
+      const int j = __builtin_ctzll(runs);
+      uint32_t st = readlane_u32(pst, j), len = readlane_u32(plen, j);
+      do {
+        const float4 c = a.ent[st + (uint32_t)lane];
+        r = __float_as_int(c.w);
+        d = sq_dist(q.qx, q.qy, q.qz, c);
+        u = order_bits(d);
+        const uint64_t in = lanes_where(r < q.m);
+        cand = in & lanes_where(u <= thr);
+        st += 64;
+        len = in == ~0ull ? len - 64 : 0;
+      } while (!cand && len >= 64);
+      pst = writelane_u32(st, j, pst);
+      plen = writelane_u32(len, j, plen);
+      if (len == 0) pend &= ~(1ull << j);
+    } else {
+      // descriptors of the next unexpanded sites (about 4 fit a batch)
+      uint64_t dsc = __builtin_nondeterministic_value(dsc), win = 0;
+      if (open) {
+        win = open & (0xffull << __builtin_ctzll(open));
+        if (in_mask(win)) dsc = a.lst[(uint32_t)w.r_of(N)];
       }
-    };
-    while (pend) {
-      const int j = pop_lane(pend);
-      lay(readlane_u32(pst, j), readlane_u32(plen, j));
+      const uint32_t dst = (uint32_t)dsc, dlen = (uint32_t)(dsc >> 32);
+      // ---- lay the lists over the lanes.  The i-th list starts at the i-th set bit of
+      //      `starts`; lane i of `at` holds its first entry's index less that lane
+      uint32_t at = __builtin_nondeterministic_value(at), rest = __builtin_nondeterministic_value(rest);
+      uint32_t total = 0;
+      uint64_t starts = 0, cut = 0;
+      int lists = 0;
+      auto lay = [&](uint32_t st, uint32_t len) {
+        at = writelane_u32(st - total, lists, at);
+        ++lists;
+        set_bit(starts, total);
+        const uint32_t room = min(cap, 64u - total);
+        total += min(len, room);
+        if (len > room) {
+          set_bit(cut, total - 1);
+          rest = writelane_u32(len - room, (int)total - 1, rest);
+        }
+      };
+      while (pend) {
+        const int j = pop_lane(pend);
+        lay(readlane_u32(pst, j), readlane_u32(plen, j));
+      }
+      uint64_t left = win & lanes_where(dlen != 0);
+      while (left) {
+        if (total >= 64) break;
+        const int j = pop_lane(left);
+        lay(readlane_u32(dst, j), readlane_u32(dlen, j));
+      }
+      N |= in_mask(win & ~left) ? 1u : 0u;   // an empty list is expanded already
+      if (total == 0) continue;
+      // ---- the batch's entries.  Lanes past the last list read on behind it (the arena is
+      //      padded for that) and are left out
+      const uint32_t base = lane_value(at, lanes_below(starts >> 1));
+      const float4 c = a.ent[base + (uint32_t)lane];
+      r = __float_as_int(c.w);
+      const uint64_t in = lanes_where(r < q.m) & (~0ull >> (64 - total));
+      d = sq_dist(q.qx, q.qy, q.qz, c);
+      u = order_bits(d);
+      if (cut) {   // ascending ranks: a list goes on if its last entry here is in the prefix
+        pend = cut & in;
+        pst = base + (uint32_t)lane + 1u;
+        plen = rest;
+      }
+      cand = in & lanes_where(u <= thr);
     }
-    uint64_t left = win & lanes_where(dlen != 0);
-    while (left) {
-      if (total >= 64) break;
-      const int j = pop_lane(left);
-      lay(readlane_u32(dst, j), readlane_u32(dlen, j));
-    }
-    N |= in_mask(win & ~left) ? 1u : 0u;   // an empty list is expanded already
-    if (total == 0) continue;
-    // ---- the batch's entries.  Lanes past the last list read on behind it (the arena is
-    //      padded for that) and are left out
-    const uint32_t base = lane_value(at, lanes_below(starts >> 1));
-    const float4 c = a.ent[base + (uint32_t)lane];
-    r = __float_as_int(c.w);
-    const uint64_t in = lanes_where(r < q.m) & (~0ull >> (64 - total));
-    d = sq_dist(q.qx, q.qy, q.qz, c);
-    const uint32_t u = order_bits(d);
-    if (cut) {   // ascending ranks: a list goes on if its last entry here is in the prefix
-      pend = cut & in;
-      pst = base + (uint32_t)lane + 1u;
-      plen = rest;
-    }
-    const uint64_t cand = in & lanes_where(u <= thr);
     if (!cand) continue;
     if (nseen > kWaveSeen - 128) {   // keep the table sparse: only N's ranks still matter
       clear_seen(w.seen, lane);

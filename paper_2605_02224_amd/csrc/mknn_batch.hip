@@ -45,6 +45,7 @@
 #include <vector>
 
 #include "device_common.h"
+#include "launch_rule.h"
 #include "knn_group.h"
 #include "knn_rows.h"
 #include "knn_wave.h"
@@ -653,10 +654,14 @@ static mknn_status plan_run(mknn_batch_plan *p, const mknn_request *reqs, int32_
   }
   for (int32_t r = 0; r <= nreq; ++r) d_qoff[r] = qoff[r];
   // ---- run (graph replay or eager)
-  // classes of more than 16 neighbours whose requests all search their whole cloud
+  // classes of more than 16 neighbours whose requests all search their whole cloud, none of
+  // them with a hub (see walk_for())
   for (int c = 0; c < kClasses; ++c) hdr->by_wave[c] = c > 0 && !p->persistent;
   for (int32_t r = 0; r < nreq; ++r)
-    if (args[r].m < args[r].n && reqs[r].nq > 0) hdr->by_wave[cls[r]] = 0;
+    if (reqs[r].nq > 0 &&
+        (args[r].m < args[r].n ||
+         hub_lists({reqs[r].nq, kwalk[r], false, args[r].m, args[r].n, reqs[r].cloud->dev_longest})))
+      hdr->by_wave[cls[r]] = 0;
   uint32_t need = 0;   // the classes with work in this batch
   for (int c = 0; c < kClasses; ++c)
     if (class_q[c] > 0) need |= 1u << (hdr->by_wave[c] ? c + 4 : c);

@@ -31,6 +31,7 @@
 #include <vector>
 
 #include "device_common.h"
+#include "launch_rule.h"
 #include "knn_group.h"
 #include "knn_rows.h"
 #include "knn_scan.h"
@@ -217,18 +218,6 @@ constexpr int kScanBlock = 1024;
 constexpr int kScanBlocks = kMortonBins / kScanBlock;
 static_assert(kScanBlocks <= 1024, "one workgroup scans the block totals");
 constexpr int64_t kSortMinQueries = 8192;
-// Sizes between which walk_for() chooses.
-constexpr int64_t kSmallQueries = 16384, kLargeQueries = 65536;
-// The wave kernel gains less from neighbours in a wavefront than the bucketing costs (five
-// launches, 20 us and up) until launches are larger: 1M-point torus, k = 16, 65536 queries 182
-// us as they come, 215 us bucketed; 262144 queries 594 and 590; 1000000 queries 2081 and 1928.
-// With long rows, or the plane fit's gather of their points, it pays from half as many: 200k
-// queries over 200k points, k = 64 1.42 and 1.33 ms, k = 20 with planes 714 and 692 us.
-constexpr int64_t kWaveSortQueries = 262144;
-static int64_t wave_sort_min(int kmax, bool planes) {
-  return kmax > 32 || planes ? kWaveSortQueries / 2 : kWaveSortQueries;
-}
-
 // The histogram's atomic hands every query its rank within its bin, so the scatter below
 // places it with no atomic of its own.
 __global__ __launch_bounds__(256) void morton_hist_kernel(const float *q, int64_t nq, BoxArgs b,
@@ -333,9 +322,9 @@ void release_old_arena(DeviceDelta *d) {
 
 // ---- the device image of the lists
 // List placement: `order` gets the owners in Morton order (older first within a code), `lst`
-// every list's descriptor, *cap the records to allocate.
+// every list's descriptor, *cap the records to allocate, *longest the entries of the longest.
 static mknn_status place_lists(mknn_cloud *c, std::vector<int32_t> *order,
-                               std::vector<uint64_t> *lst, int64_t *cap) {
+                               std::vector<uint64_t> *lst, int64_t *cap, int64_t *longest) {
   const int64_t n = c->n;
   const BoxArgs b = box_of(c);
   std::vector<uint32_t> code(n);
@@ -361,13 +350,15 @@ static mknn_status place_lists(mknn_cloud *c, std::vector<int32_t> *order,
   if (*cap > (int64_t)0xffffffffll)
     return set_error(MKNN_EUNSUPPORTED, "mknn_upload: more than 2^32 list entries");
   lst->resize((size_t)n);
-  uint64_t cur = 0;
+  uint64_t cur = 0, most = 0;
   for (int64_t t = 0; t < n; ++t) {
     const int64_t r = (*order)[t];
     const uint64_t len = (uint64_t)(c->succ.off[r + 1] - c->succ.off[r]);
     (*lst)[r] = cur | (len << 32);
     cur += len;
+    most = std::max(most, len);
   }
+  *longest = (int64_t)most;
   return MKNN_OK;
 }
 
@@ -375,7 +366,7 @@ mknn_status pack_lists(mknn_cloud *c, HostPack *p) {
   try {
     const int64_t n = c->n;
     std::vector<int32_t> order;
-    const mknn_status st = place_lists(c, &order, &p->lst, &p->cap);
+    const mknn_status st = place_lists(c, &order, &p->lst, &p->cap, &p->longest);
     if (st != MKNN_OK) return st;
     const int64_t nnz = (int64_t)c->succ.ent.size();
     p->ent.assign((size_t)(nnz + kEntPad) * 4, 0.f);
@@ -446,7 +437,7 @@ struct Arena {
     return set_error(e == hipErrorOutOfMemory ? MKNN_ENOMEM : MKNN_EHIP,
                      std::string("mknn_upload: ") + hipGetErrorName(e));
   }
-  void give(mknn_cloud *c, int64_t nnz) {
+  void give(mknn_cloud *c, int64_t nnz, int64_t longest) {
     c->d_ent = ent;
     c->d_lst = lst;
     c->d_pts = pts;
@@ -455,6 +446,7 @@ struct Arena {
     c->lst_cap = lst_cap;
     c->ent_used = nnz;
     c->ent_cap = cap - kEntPad;
+    c->dev_longest = longest;
     note_device_state(c);
     c->dev_version = c->version.load();
   }
@@ -473,7 +465,7 @@ mknn_status install_pack(mknn_cloud *c, const HostPack *p, hipStream_t s) {
   if (e == hipSuccess)
     e = hipMemcpyAsync(m.pts, p->pts.data(), sizeof(float) * p->pts.size(), hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return m.fail(e);
-  m.give(c, p->nnz);
+  m.give(c, p->nnz, p->longest);
   return MKNN_OK;
 }
 
@@ -484,9 +476,9 @@ static mknn_status install_gathered(mknn_cloud *c, int dev, hipStream_t s) {
   std::vector<int32_t> order;
   std::vector<uint64_t> lst;
   std::vector<float> pts;
-  int64_t cap = 0;
+  int64_t cap = 0, longest = 0;
   try {
-    const mknn_status st = place_lists(c, &order, &lst, &cap);
+    const mknn_status st = place_lists(c, &order, &lst, &cap, &longest);
     if (st != MKNN_OK) return st;
     pts.assign((size_t)c->n * 4, 0.f);
     for (int64_t r = 0; r < c->n; ++r)
@@ -520,7 +512,7 @@ static mknn_status install_gathered(mknn_cloud *c, int dev, hipStream_t s) {
   if (off) (void)hipFreeAsync(off, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return m.fail(e);
-  m.give(c, nnz);
+  m.give(c, nnz, longest);
   return MKNN_OK;
 }
 
@@ -647,6 +639,7 @@ mknn_status apply_delta(mknn_cloud *c, DeviceDelta *d, hipStream_t s) {
   HIP_TRY(hipGetLastError(), "apply list delta: launch");
   HIP_TRY(hipFreeAsync(d_tmp, s), "apply list delta: free scratch");
   c->ent_used += need;
+  for (uint32_t len : d->lens) c->dev_longest = std::max<int64_t>(c->dev_longest, len);
   note_device_state(c);
   c->dev_version = c->version.load();
   return MKNN_OK;
@@ -694,38 +687,11 @@ static long env_long(const char *name, long dflt) {
 // from 8 candidates per chunk on.
 constexpr TuneConfig kDefaultConfig = {3, 8, 4};
 
-// Rows or wavefronts.  The wave kernel's steps are short (a query's critical path is half the
-// row kernel's), the row kernel's lanes are fuller for short rows of many queries.  us per
-// launch over a 1M-point torus, rows (bucketed) / wave (bucketed from kWaveSortQueries on):
-//   queries      k=1         k=8          k=16         k=20         k=32         k=64
-//   10000       51 / 26     69 / 43      89 / 52     111 / 58     140 / 72     248 / 168
-//   32768       51 / 34     90 / 77     122 / 102    152 / 114    195 / 152    375 / 327
-//   65536       76 / 50    136 / 134    188 / 182    241 / 207    312 / 277    633 / 525
-//   98304      101 / 81    182 / 200    255 / 268    328 / 305    433 / 407    899 / 708
-//   262144     213 / 172   397 / 430    567 / 590    730 / 676    990 / 917   2071 / 1591
-//   1000000    695 / 534  1388 / 1433  1947 / 1928  2507 / 2199  3373 / 2974  7195 / 5374
-// Prefixes cut lists short, which leaves the wave kernel's batches half empty; the scan kernel
-// drops a list where the prefix ends, and the rows lose least.  Over 400k points, rows / wave /
-// scan, prefix of 100k: 65536 queries k=8 114 / 145 / 133, k=32 268 / 352 / 297, k=64 579 / 720 /
-// 576; 500k queries k=16 680 / 1139 / 866, k=20 1067 / 1337 / 986, k=64 3622 / 3724 / 2447; 20000
-// queries k=32 131 / 148 / 206; 4096 queries k=16 50 / 39 / 52.  A k and prefix per query
-// (prefixes of 400 to 400k; all 400k): 20000 queries k <= 32 236 / 207 / 207 (250 / 184 / 218);
-// 131072 queries k <= 16 390 / 372 / 346 (409 / 338 / 389); 500k queries k <= 16 878 / 983 / 890
-// (944 / 871 / 965), k <= 32 1414 / 1418 / 1147 (1464 / 1145 / 1243).
-enum class Walk { kRows, kWaves, kScan };
-static Walk walk_for(int kmax, bool uniform, bool prefix, int64_t nq) {
+// The rule's choice of kernel, unless MKNN_KERNEL names one.
+static Walk walk_of(const LaunchSize &l) {
   static const char *const v = getenv("MKNN_KERNEL");
   if (v) return v[0] == 'w' ? Walk::kWaves : v[0] == 's' ? Walk::kScan : Walk::kRows;
-  if (nq <= kSmallQueries || (uniform && kmax == 1)) return Walk::kWaves;
-  if (!uniform) {
-    if (nq <= kLargeQueries) return Walk::kWaves;
-    return kmax <= 16 && nq > kWaveSortQueries ? Walk::kRows : Walk::kScan;
-  }
-  if (prefix) {
-    const int64_t scan_min = kmax > 32 ? kLargeQueries : kWaveSortQueries;
-    return kmax > 16 && nq >= scan_min ? Walk::kScan : Walk::kRows;
-  }
-  return nq <= kLargeQueries || kmax > 16 ? Walk::kWaves : Walk::kRows;
+  return walk_for(l);
 }
 
 static std::mutex g_tune_mu;
@@ -874,12 +840,12 @@ static hipError_t launch_wave(const QueryArgs &a, int32_t per_wave, bool scan, h
   return hipGetLastError();
 }
 
-static hipError_t dispatch_wave(const QueryArgs &a, int kmax, bool scan, hipStream_t s) {
-  const WaveShape w = wave_shape(a.nq, kmax);
-  if (kmax <= 16)
+static hipError_t dispatch_wave(const QueryArgs &a, const LaunchSize &l, bool scan, hipStream_t s) {
+  const WaveShape w = wave_shape(l, 32 * (int64_t)device_cus());
+  if (l.kmax <= 16)
     return w.lanes == 8 ? launch_wave<8, 16>(a, w.per_wave, scan, s)
                         : launch_wave<16, 16>(a, w.per_wave, scan, s);
-  if (kmax <= 32)
+  if (l.kmax <= 32)
     return w.lanes == 8 ? launch_wave<8, 32>(a, w.per_wave, scan, s)
                         : launch_wave<16, 32>(a, w.per_wave, scan, s);
   return launch_wave<16, 64>(a, w.per_wave, scan, s);
@@ -959,13 +925,13 @@ static mknn_status run_query(const mknn_cloud *c, const float *d_q, int64_t nq, 
   a.cnt_lists = d_cl;
   a.cnt_inserts = d_ci;
   const bool exact = (d_k == nullptr);
-  const Walk walk =
-      force || d_ce ? Walk::kRows : walk_for(kmax, exact, exact && m < c->dev_n, nq);
+  const LaunchSize size = {nq, kmax, !exact, m, c->dev_n, c->dev_longest};
+  const Walk walk = force || d_ce ? Walk::kRows : walk_of(size);
   void *scratch = nullptr;
   float4 *qs = nullptr;
   mknn_status st = prepare_queries(c, d_q, nq, s,
                                    walk == Walk::kRows ? kSortMinQueries
-                                                       : wave_sort_min(kmax, d_plane != nullptr),
+                                                       : wave_sort_min(size, d_plane != nullptr),
                                    &qs, &scratch, fixed_scratch);
   if (st != MKNN_OK) return st;
   a.qs = qs;
@@ -979,7 +945,7 @@ static mknn_status run_query(const mknn_cloud *c, const float *d_q, int64_t nq, 
   hipError_t e = fixed_scratch ? hipSuccess : timing_mark(s, true);
   if (e == hipSuccess) {
     if (walk != Walk::kRows)
-      e = dispatch_wave(a, kmax, walk == Walk::kScan, s);
+      e = dispatch_wave(a, size, walk == Walk::kScan, s);
     else if (cfg.family == 1)
       e = d_ce ? dispatch_lane<true>(a, kmax, exact, s) : dispatch_lane<false>(a, kmax, exact, s);
     else if (cfg.family == 3 && !d_ce)

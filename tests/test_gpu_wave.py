@@ -230,3 +230,64 @@ def test_last_position_fills_within_an_insertion(env, sites, jitter):
         k = min(48, sites - 16)
         idx, _ = _rows(torch, cl, Q, k, sites)
         assert np.array_equal(idx, _exact_rows(P, Q, k, sites, live)), (n, "pending")
+
+
+@pytest.fixture(scope="module")
+def hubs(env):
+    """Clouds with lists that are a good part of them: a sphere around its centre, the oldest
+    point; a sheet and a few points far off it."""
+    torch, oracle, A, W, _, _ = env
+    rng = np.random.default_rng(7)
+    s = rng.standard_normal((9000, 3))
+    s *= (1 + 1e-3 * rng.standard_normal((9000, 1))) / np.linalg.norm(s, axis=1, keepdims=True)
+    s[0] = 0
+    xy = rng.random((8980, 2))
+    out = np.r_[np.c_[xy, 0.1 * np.sin(9 * xy[:, 0])], 10 * rng.random((20, 3))][rng.permutation(9000)]
+    clouds = {}
+    for name, P in (("centre", s), ("outliers", out)):
+        P = P.astype(np.float32)
+        cl = A.Cloud.build(P).upload()
+        off, _ = cl.successors()
+        assert (off[1:] - off[:-1]).max() > (4096 if name == "centre" else 1024)
+        clouds[name] = (P, cl)
+    return clouds
+
+
+@pytest.mark.parametrize("nq", [300, 9000, 70001])
+@pytest.mark.parametrize("name", ["centre", "outliers"])
+def test_long_lists(env, hubs, name, nq):
+    """Lists of thousands of entries, read 64 at a time to their end or the prefix's: ranks equal
+    the FP64 brute force's (near-ties excused)."""
+    torch, oracle, A, W, _, _ = env
+    P, cl = hubs[name]
+    rng = np.random.default_rng(nq)
+    Q = W.uniform_in_box(rng, nq, *W.bbox_expanded(P, 1.1))
+    pick = np.sort(rng.choice(nq, 300, replace=False))
+    for m in (9000, 2500):
+        ri, _, rD = oracle.knn_bruteforce(P, Q[pick], 65, m)
+        for k in (1, 8, 20, 32, 64):
+            idx, dist = _rows(torch, cl, Q, k, m)
+            assert compare_rows(idx[pick], dist[pick], ri[:, :k], rD[:, :k], rD[:, k], P=P, Q=Q[pick],
+                                m=m) <= 2, (k, m)
+    q = torch.from_numpy(Q).cuda()
+    for kmax in (4, 32):
+        kq = rng.integers(1, kmax + 1, nq).astype(np.int32)
+        mq = rng.integers(1, 9001, nq).astype(np.int32)
+        idx, dist, off = cl.knn_var(q, torch.from_numpy(kq).cuda(), torch.from_numpy(mq).cuda())
+        torch.cuda.synchronize()
+        idx, dist, off = idx.cpu().numpy(), dist.cpu().numpy(), off.cpu().numpy()
+        ex = 0
+        for i in pick[:60]:
+            ri, _, rD = oracle.knn_bruteforce(P, Q[i:i + 1], int(kq[i]), int(mq[i]))
+            ex += compare_rows(idx[None, off[i]:off[i + 1]], dist[None, off[i]:off[i + 1]], ri, rD, P=P,
+                               Q=Q[i:i + 1], m=int(mq[i]))
+        assert ex <= 2
+    items = A.alloc_outputs([(cl, q[:2000].contiguous(), k, None) for k in (8, 20, 40, 64)])
+    plan = A.BatchPlan(4, 8000)
+    plan.run(items)
+    torch.cuda.synchronize()
+    for it in items:
+        ri, rd = cl.knn(it[1], it[2])
+        torch.cuda.synchronize()
+        assert torch.equal(it[4], ri) and torch.equal(it[5], rd)
+    plan.close()
