@@ -27,8 +27,8 @@
 // read, a wave-wide shift by one lane and a median of three, whatever k is.  Keys that agree
 // in the upper 24 bits are not ordered by the map; nothing depends on their order until
 //   - the end, where neighbours in the row that agree are ordered by their exact keys,
-//   - a key that is dropped past lane 63 while it agrees with the k-th: the query is then
-//     answered again by answer_exact(), which keeps exact keys in the lanes.
+//   - a key that is dropped past lane 63 while it agrees with the k-th: keep_nearest() then
+//     decides by the exact keys, which are still in their slots, which of them stay.
 // Sites already offered are recognised by rank in an open-addressed table in LDS.
 //
 // Measured, against the row kernel: 2000 queries of k=20 26 us for 63; 200k of k=64 1.33 ms for
@@ -266,7 +266,7 @@ __device__ __forceinline__ void write_row(const QueryArgs &a, const WaveQuery &q
 
 // Alg. 1 and Alg. 2 as written, one list after the other, the whole wavefront on one query,
 // with the exact keys (D, rank) of N in the lanes.  For queries whose first distance is not
-// finite, and those with more sites tied at the k-th distance than 32-bit keys can hold.
+// finite (and, in the scan kernel, those with sites tied in their keys that it cannot order).
 __device__ __forceinline__ void answer_exact(const QueryArgs &a, const WaveQuery &q, int lane) {
   double d = INFINITY;
   int32_t r = kEmpty;
@@ -336,6 +336,41 @@ __device__ __forceinline__ void answer_exact(const QueryArgs &a, const WaveQuery
 // The record of a ring entry.
 __device__ __forceinline__ float4 ring_site(const QueryArgs &a, uint32_t e) {
   return e == kHeadRecord ? make_float4(a.hx, a.hy, a.hz, __int_as_float(a.head)) : a.ent[e];
+}
+
+// N holds the 64 smallest keys of `before` and of the new keys `x`, and keys that fell out agree
+// with the k-th in their upper bits (they are <= thr): N with the nearest of those that agree,
+// by their exact keys.  At k = 64 every key that falls out next to one like it comes here, a few
+// in a hundred queries of most clouds and several in each where a query is far from all points
+// or amid a shell; answering those again with exact keys, as before, took as long as the rest:
+// 4096 queries of k=64 over 400k points 129 us, now 60, 200k over 200k points with far outliers 51
+// ms, now 18.5.
+template <int DW, int R>
+__device__ __forceinline__ uint32_t keep_nearest(WaveLds<DW, R> &w, uint32_t N, uint32_t before,
+                                                 uint32_t x, uint32_t thr, int lane) {
+  x = merge_rows(sort_rows(x, lane), lane);
+  const uint32_t lost = max(before, lane_value(x, 63 - lane));
+  uint64_t out = lanes_where(lost <= thr);
+  while (out) {
+    const uint32_t o = readlane_u32(lost, pop_lane(out));
+    const double d = w.d_of(N);
+    const int32_t r = w.r_of(N);
+    uint64_t agree = lanes_where((N ^ o) <= kTieBits);   // the k-th is among them
+    int far = pop_lane(agree);
+    double fd = readlane_f64(d, far);
+    int32_t fr = __builtin_amdgcn_readlane(r, far);
+    while (agree) {
+      const int j = pop_lane(agree);
+      const double jd = readlane_f64(d, j);
+      const int32_t jr = __builtin_amdgcn_readlane(r, j);
+      const bool farther = key_less(fd, fr, jd, jr);
+      far = farther ? j : far;
+      fd = farther ? jd : fd;
+      fr = farther ? jr : fr;
+    }
+    if (key_less(w.d_of(o), w.r_of(o), fd, fr)) N = writelane_u32(o, far, N);
+  }
+  return merge_rows(sort_rows(N, lane), lane);
 }
 
 // Alg. 2 for query t of the wavefront.  All control flow is uniform.  False: to be answered
@@ -496,6 +531,8 @@ __device__ __forceinline__ bool expand(const QueryArgs &a, WaveLds<DW, R> &w, co
     nslot += nc;
     wave_lds_sync();
     // ---- insert
+    const uint32_t before = N;
+    const uint64_t added = fresh;
     uint32_t lost = kPadKey;   // keys that fall out of the lanes
     if (nc <= kWaveInsert) {
       // one by one: every position keeps the middle of its key, the one before and the new.
@@ -525,7 +562,10 @@ __device__ __forceinline__ bool expand(const QueryArgs &a, WaveLds<DW, R> &w, co
     }
     nreal = min(64, nreal + nc);
     thr = min(readlane_u32(N, q.k - 1) | kTieBits, kMaxKey);
-    if (nreal == 64 && lanes_where(lost <= thr)) return false;   // agrees with the k-th
+    if (nreal == 64 && lanes_where(lost <= thr)) {   // agrees with the k-th
+      N = keep_nearest(w, N, before, in_mask(added) ? key : kPadKey, thr, lane);
+      thr = min(readlane_u32(N, q.k - 1) | kTieBits, kMaxKey);
+    }
   }
   // ---- the exact keys, and the order of those whose upper bits agree
   d = INFINITY;

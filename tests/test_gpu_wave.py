@@ -291,3 +291,25 @@ def test_long_lists(env, hubs, name, nq):
         torch.cuda.synchronize()
         assert torch.equal(it[4], ri) and torch.equal(it[5], rd)
     plan.close()
+
+
+@pytest.mark.parametrize("k", [33, 48, 63, 64])
+def test_keys_that_agree(env, k):
+    """Queries near the middle of a shell: the distances of all sites agree in the upper bits of
+    their keys, so which of them are the k nearest is decided by the exact ones alone."""
+    torch, oracle, A, W, _, _ = env
+    rng = np.random.default_rng(k)
+    for spread in (0.0, 1e-7, 1e-4):
+        P = rng.standard_normal((600, 3))
+        P *= (1 + spread * rng.standard_normal((600, 1))) / np.linalg.norm(P, axis=1, keepdims=True)
+        P = P.astype(np.float32)
+        cl = A.Cloud.build(P).upload()
+        Q = (1e-7 * rng.standard_normal((200, 3))).astype(np.float32)
+        Q[:60] = 0
+        Q[60:90] *= 1e9
+        for m in (600, 66, 200):
+            idx, dist = _rows(torch, cl, Q, k, m)
+            ri, _, rD = oracle.knn_bruteforce(P, Q, k + 1, m)
+            # (near-ties, which are all of the sites here, may stand for each other; the rest of
+            # the rule holds: true distances, ordered by (D, age), no rank twice)
+            compare_rows(idx, dist, ri[:, :k], rD[:, :k], rD[:, k], P=P, Q=Q, m=m)
