@@ -16,6 +16,8 @@ struct LaunchSize {
   int64_t longest = 0;      // entries of the cloud's longest list
 };
 
+// Launches by rows are bucketed from here on.
+constexpr int64_t kSortMinQueries = 8192;
 // Sizes between which walk_for() chooses.
 constexpr int64_t kSmallQueries = 16384, kLargeQueries = 65536;
 // The wave kernel gains less from neighbours in a wavefront than the bucketing costs (five
@@ -57,6 +59,10 @@ inline bool hub_lists(const LaunchSize &l) {
 // (prefixes of 400 to 400k; all 400k): 20000 queries k <= 32 236 / 207 / 207 (250 / 184 / 218);
 // 131072 queries k <= 16 390 / 372 / 346 (409 / 338 / 389); 500k queries k <= 16 878 / 983 / 890
 // (944 / 871 / 965), k <= 32 1414 / 1418 / 1147 (1464 / 1145 / 1243).
+// Few queries in a prefix, rows / waves, over 400k points on a torus and in a solid: 6500 queries
+// k=2, m=100k 17.9 / 21.3 and 18.5 / 20.8, k=4, m=24k 19.5 / 21.6 and 20.7 / 23.6; 8191 queries
+// k=8, m=4k 24 / 26 and 25 / 29; 16384 queries k=32, m=100k 124 / 106 and 123 / 138, k=64 246 / 195
+// and 240 / 267 (13000 queries: waves are ahead in both).
 // Long lists: 200k queries with a k and prefix each over a height field (longest list 2755), all
 // 400k points: k <= 32 rows 1094, waves 912, scan 1073; k <= 4 563 / 526 / 695.  With a hub, larger
 // launches go by rows but for k = 1, and for k <= 16 up to kLargeQueries: a sphere and its centre
@@ -69,6 +75,13 @@ inline Walk walk_for(const LaunchSize &l) {
     return l.kmax <= 16 && l.m >= l.n && l.nq <= kLargeQueries ? Walk::kWaves : Walk::kRows;
   }
   const bool uniform = !l.per_query, prefix = uniform && l.m < l.n;
+  if (prefix && l.kmax > 1) {
+    // as many wavefronts as are resident at once, each on one short query: rows, four to a
+    // wavefront and not bucketed either, issue less
+    if (l.nq > 4096 && l.nq < kSortMinQueries && (l.kmax <= 4 || (l.kmax <= 16 && l.m < l.n / 32)))
+      return Walk::kRows;
+    if (l.nq > 13312 && l.kmax > 16 && l.nq <= kSmallQueries) return Walk::kRows;
+  }
   if (l.nq <= kSmallQueries || (uniform && l.kmax == 1)) return Walk::kWaves;
   if (!uniform) {
     if (l.nq <= kLargeQueries || (long_lists(l) && l.nq < kWaveSortQueries)) return Walk::kWaves;
@@ -103,6 +116,10 @@ inline WaveShape wave_shape(const LaunchSize &l, int64_t resident) {
   const bool eight = l.kmax == 1 || (l.kmax <= 32 && l.nq >= kWaveSortQueries);
   w.lanes = eight && !long_lists(l) && l.nq >= 8 * resident ? 8 : 16;
   w.per_wave = 1;
+  // a single neighbour has no expansion to wait for: four descents side by side as soon as they
+  // leave wavefronts enough (8191 queries over 400k points 21.1 us, one each 23.8; in a prefix of
+  // 20k 11.2 and 15.5)
+  if (l.kmax == 1 && l.nq > 3 * resident / 8) w.per_wave = 4;
   while (w.per_wave * 2 <= 64 / w.lanes && l.nq > w.per_wave * resident) w.per_wave *= 2;
   return w;
 }

@@ -217,7 +217,6 @@ constexpr int kMortonBins = 1 << kMortonBits;
 constexpr int kScanBlock = 1024;
 constexpr int kScanBlocks = kMortonBins / kScanBlock;
 static_assert(kScanBlocks <= 1024, "one workgroup scans the block totals");
-constexpr int64_t kSortMinQueries = 8192;
 // The histogram's atomic hands every query its rank within its bin, so the scatter below
 // places it with no atomic of its own.
 __global__ __launch_bounds__(256) void morton_hist_kernel(const float *q, int64_t nq, BoxArgs b,
