@@ -57,8 +57,10 @@ inline bool hub_lists(const LaunchSize &l) {
 // 576; 500k queries k=16 680 / 1139 / 866, k=20 1067 / 1337 / 986, k=64 3622 / 3724 / 2447; 20000
 // queries k=32 131 / 148 / 206; 4096 queries k=16 50 / 39 / 52.  A k and prefix per query
 // (prefixes of 400 to 400k; all 400k): 20000 queries k <= 32 236 / 207 / 207 (250 / 184 / 218);
-// 131072 queries k <= 16 390 / 372 / 346 (409 / 338 / 389); 500k queries k <= 16 878 / 983 / 890
-// (944 / 871 / 965), k <= 32 1414 / 1418 / 1147 (1464 / 1145 / 1243).
+// 70000 k <= 32 402 / 364 / 367 (414 / 309 / 399); 131072 k <= 16 375 / 375 / 354 (395 / 350 / 399),
+// k <= 32 533 / 513 / 462 (568 / 439 / 512); 200000 k <= 4 333 / 333 / 326 (358 / 362 / 373), k <= 16
+// 458 / 487 / 454 (498 / 457 / 524); 262144 k <= 4, bucketed 370 / 417 / 411 (408 / 422 / 447); 500k
+// queries k <= 16 878 / 983 / 890 (944 / 871 / 965), k <= 32 1414 / 1418 / 1147 (1464 / 1145 / 1243).
 // Few queries in a prefix, rows / waves, over 400k points on a torus and in a solid: 6500 queries
 // k=2, m=100k 17.9 / 21.3 and 18.5 / 20.8, k=4, m=24k 19.5 / 21.6 and 20.7 / 23.6; 8191 queries
 // k=8, m=4k 24 / 26 and 25 / 29; 16384 queries k=32, m=100k 124 / 106 and 123 / 138, k=64 246 / 195
@@ -85,7 +87,9 @@ inline Walk walk_for(const LaunchSize &l) {
   if (l.nq <= kSmallQueries || (uniform && l.kmax == 1)) return Walk::kWaves;
   if (!uniform) {
     if (l.nq <= kLargeQueries || (long_lists(l) && l.nq < kWaveSortQueries)) return Walk::kWaves;
-    return l.kmax <= 16 && l.nq > kWaveSortQueries ? Walk::kRows : Walk::kScan;
+    if (l.kmax > 16) return l.nq <= 98304 ? Walk::kWaves : Walk::kScan;
+    // (bucketing costs what the waves gain from it)
+    return l.nq < (l.kmax <= 4 ? kWaveSortQueries : 131073) ? Walk::kWaves : Walk::kRows;
   }
   if (prefix) {
     const int64_t scan_min = l.kmax > 32 ? kLargeQueries : kWaveSortQueries;

@@ -80,3 +80,15 @@ def test_few_queries_in_prefixes(rule):
     assert rule(*[dict(nq=nq, k=1) for nq in (3072, 3073, 8191, 16384, 65535, 65536)]) == [
         ("waves", 0, 16, 1), ("waves", 0, 16, 4), ("waves", 0, 16, 4), ("waves", 0, 16, 4),
         ("waves", 0, 16, 4), ("waves", 0, 8, 8)]
+
+
+def test_a_k_and_prefix_per_query(rule):
+    """Waves while they are not bucketed, the scan kernel only for long rows of many queries, rows
+    for short rows of many."""
+    ask = [dict(nq=nq, k=k, var=1) for nq, k in (
+        (65536, 64), (65537, 32), (98304, 17), (131072, 16), (262143, 4), (262143, 1))]
+    assert [a[0] for a in rule(*ask)] == ["waves"] * 6
+    assert [a[0] for a in rule(*[dict(nq=nq, k=k, var=1) for nq, k in (
+        (98305, 17), (131072, 64), (1000000, 32))])] == ["scan"] * 3
+    assert [a[0] for a in rule(*[dict(nq=nq, k=k, var=1) for nq, k in (
+        (131073, 5), (262144, 16), (262144, 2), (262144, 1), (1000000, 8))])] == ["rows"] * 5
