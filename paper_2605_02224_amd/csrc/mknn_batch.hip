@@ -44,6 +44,7 @@
 #include <string>
 #include <vector>
 
+#include "batch_graphs.h"
 #include "device_common.h"
 #include "launch_rule.h"
 #include "knn_group.h"
@@ -394,8 +395,9 @@ struct mknn_batch_plan {
   char *h_stage = nullptr;          // pinned
   hipStream_t cap_stream = nullptr;
   // captured graphs: [0] the plain kernels, [1] the variants that filter pending deletions
-  hipGraph_t graph[2] = {nullptr, nullptr};
-  hipGraphExec_t exec[2] = {nullptr, nullptr};
+  hipGraph_t graph[2][BatchGraphs::kDivisions] = {};
+  hipGraphExec_t exec[2][BatchGraphs::kDivisions] = {};
+  BatchGraphs graphs;
   hipEvent_t done = nullptr;
   bool pending = false;
   uint32_t grid_batch[kClasses] = {1, 1, 1, 1};
@@ -406,7 +408,6 @@ struct mknn_batch_plan {
   int32_t merge_min[kClasses] = {0, 0, 0, 0};   // per class (S - 1); 0 = the autotuner's table
   // register classes that plan_enqueue launches: bit S-1 by rows, bit S+3 by waves
   uint32_t classes = 0xF;
-  uint32_t graph_classes[2] = {0, 0};   // the classes each captured graph launches
   uint32_t grid_stream = 1;
 };
 
@@ -414,10 +415,11 @@ static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 static void plan_release(mknn_batch_plan *p) {
   if (p->pending && p->done) (void)hipEventSynchronize(p->done);
-  for (int v = 0; v < 2; ++v) {
-    if (p->exec[v]) (void)hipGraphExecDestroy(p->exec[v]);
-    if (p->graph[v]) (void)hipGraphDestroy(p->graph[v]);
-  }
+  for (int v = 0; v < 2; ++v)
+    for (int g = 0; g < BatchGraphs::kDivisions; ++g) {
+      if (p->exec[v][g]) (void)hipGraphExecDestroy(p->exec[v][g]);
+      if (p->graph[v][g]) (void)hipGraphDestroy(p->graph[v][g]);
+    }
   if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
   if (p->done) (void)hipEventDestroy(p->done);
   if (p->d_base) (void)hipFree(p->d_base);
@@ -662,21 +664,25 @@ static mknn_status plan_run(mknn_batch_plan *p, const mknn_request *reqs, int32_
         (args[r].m < args[r].n ||
          hub_lists({reqs[r].nq, kwalk[r], false, args[r].m, args[r].n, reqs[r].cloud->dev_longest})))
       hdr->by_wave[cls[r]] = 0;
-  uint32_t need = 0;   // the classes with work in this batch
-  for (int c = 0; c < kClasses; ++c)
-    if (class_q[c] > 0) need |= 1u << (hdr->by_wave[c] ? c + 4 : c);
+  uint32_t work = 0, waves = 0;   // the classes with work in this batch; those by waves
+  for (int c = 0; c < kClasses; ++c) {
+    if (class_q[c] > 0) work |= 1u << c;
+    if (class_q[c] > 0 && hdr->by_wave[c]) waves |= 1u << c;
+  }
   if (p->use_graph && !timing_enabled()) {
     const int v = any_lazy ? 1 : 0;
-    if (p->exec[v] && (need & ~p->graph_classes[v])) {
+    const BatchGraphs::Choice c = p->graphs.choose(v, work, waves);
+    hipGraph_t &graph = p->graph[v][c.graph];
+    hipGraphExec_t &exec = p->exec[v][c.graph];
+    if (exec && c.grown) {
       // a class the graph does not launch: capture again with it (the previous run is done)
-      (void)hipGraphExecDestroy(p->exec[v]);
-      (void)hipGraphDestroy(p->graph[v]);
-      p->exec[v] = nullptr;
-      p->graph[v] = nullptr;
+      (void)hipGraphExecDestroy(exec);
+      (void)hipGraphDestroy(graph);
+      exec = nullptr;
+      graph = nullptr;
     }
-    if (!p->exec[v]) {
-      p->classes = p->graph_classes[v] | need;
-      p->graph_classes[v] = p->classes;
+    if (!exec) {
+      p->classes = c.launch;
       HIP_TRY(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal),
               "mknn_batch_plan_run: begin capture");
       hipError_t e = plan_enqueue(p, p->cap_stream, any_lazy);
@@ -687,13 +693,18 @@ static mknn_status plan_run(mknn_batch_plan *p, const mknn_request *reqs, int32_
         return set_error(MKNN_EHIP, std::string("mknn_batch_plan_run: capture failed: ") +
                                         hipGetErrorName(e != hipSuccess ? e : e2));
       }
-      p->graph[v] = g;
-      HIP_TRY(hipGraphInstantiate(&p->exec[v], p->graph[v], nullptr, nullptr, 0),
-              "mknn_batch_plan_run: instantiate");
+      graph = g;
+      const hipError_t e3 = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+      if (e3 != hipSuccess) {
+        (void)hipGraphDestroy(graph);
+        graph = nullptr;
+        exec = nullptr;
+        HIP_TRY(e3, "mknn_batch_plan_run: instantiate");
+      }
     }
-    HIP_TRY(hipGraphLaunch(p->exec[v], s), "mknn_batch_plan_run: graph launch");
+    HIP_TRY(hipGraphLaunch(exec, s), "mknn_batch_plan_run: graph launch");
   } else {
-    p->classes = need;
+    p->classes = (work & ~waves) | (waves << 4);
     HIP_TRY(plan_enqueue(p, s, any_lazy), "mknn_batch_plan_run: launch");
   }
   p->lazy_run = any_lazy;
