@@ -41,6 +41,10 @@ inline bool hub_lists(const LaunchSize &l) {
   return l.longest > 4096 && l.longest > l.n / 64;
 }
 
+// Single neighbours with a hub, by waves, are bucketed from here on, and by rows before (20000
+// queries of the sphere and its centre below: rows 362 us, waves as they come 393).
+constexpr int64_t kHubSortQueries = 32768;
+
 // Rows or wavefronts.  The wave kernel's steps are short (a query's critical path is half the
 // row kernel's), the row kernel's lanes are fuller for short rows of many queries.  us per
 // launch over a 1M-point torus, rows (bucketed) / wave (bucketed from kWaveSortQueries on):
@@ -73,7 +77,7 @@ inline bool hub_lists(const LaunchSize &l) {
 inline Walk walk_for(const LaunchSize &l) {
   if (hub_lists(l) && l.nq > 8192) {
     if (l.per_query) return Walk::kRows;
-    if (l.kmax == 1) return Walk::kWaves;
+    if (l.kmax == 1) return l.nq > kSmallQueries && l.nq < kHubSortQueries ? Walk::kRows : Walk::kWaves;
     return l.kmax <= 16 && l.m >= l.n && l.nq <= kLargeQueries ? Walk::kWaves : Walk::kRows;
   }
   const bool uniform = !l.per_query, prefix = uniform && l.m < l.n;
@@ -102,7 +106,7 @@ inline Walk walk_for(const LaunchSize &l) {
 // hub earlier: the descents that end in its list then share their wavefronts (sphere and centre,
 // 200k queries 1270 us as they come, 552 bucketed).
 inline int64_t wave_sort_min(const LaunchSize &l, bool planes) {
-  if (l.kmax == 1 && hub_lists(l)) return 32768;
+  if (l.kmax == 1 && hub_lists(l)) return kHubSortQueries;
   return l.kmax > 32 || planes ? kWaveSortQueries / 2 : kWaveSortQueries;
 }
 

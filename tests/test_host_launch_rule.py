@@ -54,6 +54,8 @@ def test_hubs(rule):
                                  for k in (4, 32)])] == ["rows"] * 6
     assert [a[0] for a in rule(*[dict(nq=nq, k=32, m=20000, **hub) for nq in (10000, 70000, 500000)])] == ["rows"] * 3
     assert rule(dict(nq=200000, k=1, **hub)) == [("waves", 1, 16, 4)]
+    assert [a[:2] for a in rule(*[dict(nq=nq, k=1, **hub) for nq in (16384, 16385, 32767, 32768)])] == [
+        ("waves", 0), ("rows", 0), ("rows", 0), ("waves", 1)]
 
 
 def test_long_lists(rule):
