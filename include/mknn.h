@@ -250,7 +250,9 @@ mknn_status mknn_batch_plan_run(mknn_batch_plan *plan, const mknn_request *reqs,
  * every register class with work (candidates per chunk from which the merge network
  * replaces one-by-one insertion: 4, 6, 8 for k <= 16; 5, 8, 11, 14, 17 above), one class
  * at a time; the plan keeps the fastest per class, and *best receives the threshold of the
- * class with the most queries.  Persistent launch: the tile length (8, 16, 32, 64, 256);
+ * class with the most queries.  A class of k > 16 whose requests all search their whole cloud
+ * goes by waves, which have no threshold, unless rows are faster by more than 1%; the threshold
+ * kept is for its batches by rows.  Persistent launch: the tile length (8, 16, 32, 64, 256);
  * the plan keeps the fastest and *best receives it.  The outputs hold the batch's results
  * afterwards. */
 mknn_status mknn_batch_plan_tune(mknn_batch_plan *plan, const mknn_request *reqs, int32_t nreq,
@@ -266,15 +268,19 @@ mknn_status mknn_batch_knn(const mknn_request *reqs, int32_t nreq, void *stream)
 /* ---------------------------------------------------------------------------------------
  * Autotuner.
  *
- * The query kernels come in three families -- one query per lane (register list of k
- * entries), 16 lanes per query in lockstep, and 16 lanes per query with every row scheduled
- * independently -- and, for k <= 16, switch from one-by-one candidate insertion to a
- * merge network above a number of candidates per chunk.  mknn_autotune times every
- * candidate configuration on the given queries (device float32 [nq][3], k, prefix m; m = 0
- * means n) with HIP events on `stream`, keeps the fastest for clouds of this size class
- * (log2 n) and this k class on the current device, and reports the timings.  Later
- * mknn_knn / mknn_knn_var launches and batch plans use the table; untuned classes use the
- * built-in defaults.  The table lives in the process and can be saved and loaded as text.
+ * A launch goes by rows, by waves or by scan, by a built-in rule on its query count, k, prefix
+ * and the cloud's longest list.  The kernels by rows come in three families -- one query per
+ * lane (register list of k entries), 16 lanes per query in lockstep, and 16 lanes per query
+ * with every row scheduled independently -- and switch from one-by-one candidate insertion to
+ * a merge network above a number of candidates per chunk.  mknn_autotune times these
+ * configurations on the given queries (device float32 [nq][3], k, prefix m; m = 0 means n)
+ * with HIP events on `stream`, the built-in one {3, 8, 4} as the rule runs it (by waves or
+ * scan where it says so), keeps the fastest for clouds of this size class (log2 n), this k
+ * class and launches that the rule gives to the same kernel, on the current device, and
+ * reports the timings.  Later mknn_knn / mknn_knn_var launches of that kind run the
+ * configuration kept, by rows; where it is the built-in one, and in untuned classes, the rule
+ * decides.  Batch plans take its merge threshold for the classes that they launch by rows.
+ * The table lives in the process and can be saved and loaded as text.
  *   tried      optional host array of max_tried entries, receives every candidate
  *   ntried     number of candidates timed
  *   best       the chosen configuration
@@ -283,7 +289,9 @@ mknn_status mknn_batch_knn(const mknn_request *reqs, int32_t nreq, void *stream)
  */
 typedef struct {
   int32_t family;      /* 1 lane per query, 2 lockstep rows, 3 scheduled rows */
-  int32_t merge_min;   /* k <= 16: candidates per chunk from which the merge network is used */
+  int32_t merge_min;   /* families 2, 3: candidates per chunk from which the merge network is
+                          used (launches of k = 9 .. 16 from 196608 queries on, four queries
+                          per wavefront, merge what they gather instead) */
   int32_t per_wave;    /* scheduled rows: queries per wavefront */
   float ms;            /* best of three timed runs (milliseconds) */
 } mknn_tune_entry;
@@ -292,7 +300,8 @@ mknn_status mknn_autotune(const mknn_cloud *c, const float *d_q, int64_t nq, int
                           void *stream, mknn_tune_entry *tried, int32_t max_tried,
                           int32_t *ntried, mknn_tune_entry *best);
 /* Text form of the table: a "mknn-tune 1" line, then one line per entry
- * "device S exact log2n family merge_min per_wave".  Load merges into the current table.
+ * "device S exact log2n family merge_min per_wave", followed by " waves" or " scan" if it is for
+ * launches that the rule gives to these.  Load merges into the current table.
  * Errors: EINVAL (path, malformed file), ENOTFOUND (load: no such file). */
 mknn_status mknn_tune_save(const char *path);
 mknn_status mknn_tune_load(const char *path);

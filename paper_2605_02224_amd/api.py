@@ -219,7 +219,9 @@ FAMILIES = {1: "lane", 2: "group", 3: "rows"}
 
 def autotune(cloud, q, k: int, m: Optional[int] = None, stream=None):
     """Time every kernel configuration on these queries and keep the fastest for clouds of
-    this size class and this k class.  Returns (best, tried) as dicts."""
+    this size class, this k class and launches of this kind (those that the built-in rule
+    gives to the same kernel; its own choice is timed as {"rows", 8, 4}).  Returns (best,
+    tried) as dicts."""
     tried = (_lib.TuneEntry * 16)()
     best = _lib.TuneEntry()
     n = ctypes.c_int32()

@@ -153,7 +153,9 @@ struct TuneConfig {
   int32_t per_wave;    // family 3: queries per wavefront
 };
 
-TuneConfig config_for(int kmax, bool exact, int64_t n);
+// Candidates per chunk from which a batch's class of k neighbours merges by the network (the
+// autotuner's table).
+int32_t merge_min_for(int k, int64_t n);
 
 // Optional HIP-event timing of the main query kernels (defined in mknn_device.hip).
 hipError_t timing_mark(hipStream_t s, bool start);

@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "knn_wave.h"
+#include "launch_rule.h"
 
 namespace mknn {
 
@@ -124,14 +125,6 @@ __device__ __forceinline__ void merge_exact(RowMerge::Site &a, RowMerge::Site &c
 __device__ __forceinline__ RowMerge &row_merge() {
   __shared__ RowMerge rows[16];
   return rows[threadIdx.x >> 4];
-}
-// Whether a launch (a batch's class) of nq queries gathers candidates: it takes a third fewer
-// instructions, but rows wait for each other's merges, which only other wavefronts' work hides,
-// and short rows have few lists to take meanwhile.  ms per launch over a 1M-point torus, step by
-// step / gathered: k=16 1M queries 1.95 / 1.79, 262144 0.567 / 0.538, 131072 0.316 / 0.337; k=8
-// 1M queries 1.39 / 1.40.
-__device__ __forceinline__ bool gather_rows(int32_t k, int64_t nq) {
-  return k > 8 && nq >= 196608;
 }
 constexpr uint32_t kRowTie = 0x7fu;         // number and flag: no part of the order
 constexpr uint32_t kRowPad = 0xffffff80u;   // empty position

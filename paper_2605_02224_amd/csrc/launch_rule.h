@@ -110,6 +110,13 @@ inline int64_t wave_sort_min(const LaunchSize &l, bool planes) {
   return l.kmax > 32 || planes ? kWaveSortQueries / 2 : kWaveSortQueries;
 }
 
+// Whether the rows of a launch (a batch's class) of nq queries gather candidates: it takes a third
+// fewer instructions, but rows wait for each other's merges, which only other wavefronts' work
+// hides, and short rows have few lists to take meanwhile.  ms per launch over a 1M-point torus,
+// step by step / gathered: k=16 1M queries 1.95 / 1.79, 262144 0.567 / 0.538, 131072 0.316 / 0.337;
+// k=8 1M queries 1.39 / 1.40.  Such rows know no merge threshold.
+constexpr bool gather_rows(int32_t k, int64_t nq) { return k > 8 && nq >= 196608; }
+
 // How the wave kernel lays the queries out: lanes per query in the descent, and queries per
 // wavefront (at most 64 / lanes; a second one only once every resident wavefront has one).
 // Eight queries a wavefront pay for single neighbours and for bucketed launches, 8 lanes / 16,

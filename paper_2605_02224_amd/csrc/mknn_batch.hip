@@ -406,6 +406,8 @@ struct mknn_batch_plan {
   uint32_t *h_overflow = nullptr;   // pinned: per request, rows a run could not certify
   bool lazy_run = false;            // the last run filtered pending deletions
   int32_t merge_min[kClasses] = {0, 0, 0, 0};   // per class (S - 1); 0 = the autotuner's table
+  bool rows_only[kClasses] = {};    // tuned: the class goes by rows though it could go by waves
+  uint32_t last_waves = 0;          // classes of the last run that went by waves
   // register classes that plan_enqueue launches: bit S-1 by rows, bit S+3 by waves
   uint32_t classes = 0xF;
   uint32_t grid_stream = 1;
@@ -638,7 +640,7 @@ static mknn_status plan_run(mknn_batch_plan *p, const mknn_request *reqs, int32_
     fill_cloud_args(q.cloud, &args[r]);
     const int cl = cls[r];
     args[r].merge_min = p->merge_min[cl] > 0 ? p->merge_min[cl]
-                                             : config_for(kwalk[r], false, q.cloud->dev_n).merge_min;
+                                             : merge_min_for(kwalk[r], q.cloud->dev_n);
     args[r].q = q.d_q;
     args[r].qs = p->sort ? p->d_qs + qoff[r] : nullptr;
     args[r].nq = q.nq;
@@ -658,7 +660,7 @@ static mknn_status plan_run(mknn_batch_plan *p, const mknn_request *reqs, int32_
   // ---- run (graph replay or eager)
   // classes of more than 16 neighbours whose requests all search their whole cloud, none of
   // them with a hub (see walk_for())
-  for (int c = 0; c < kClasses; ++c) hdr->by_wave[c] = c > 0 && !p->persistent;
+  for (int c = 0; c < kClasses; ++c) hdr->by_wave[c] = c > 0 && !p->persistent && !p->rows_only[c];
   for (int32_t r = 0; r < nreq; ++r)
     if (reqs[r].nq > 0 &&
         (args[r].m < args[r].n ||
@@ -669,6 +671,7 @@ static mknn_status plan_run(mknn_batch_plan *p, const mknn_request *reqs, int32_
     if (class_q[c] > 0) work |= 1u << c;
     if (class_q[c] > 0 && hdr->by_wave[c]) waves |= 1u << c;
   }
+  p->last_waves = waves;
   if (p->use_graph && !timing_enabled()) {
     const int v = any_lazy ? 1 : 0;
     const BatchGraphs::Choice c = p->graphs.choose(v, work, waves);
@@ -876,7 +879,9 @@ mknn_status mknn_batch_plan_tune(mknn_batch_plan *p, const mknn_request *reqs, i
     report = p->tile_q;
   } else {
     // the flat launch: the merge threshold of every register class with work, one class at
-    // a time (the others at their current value); the class with most queries is reported
+    // a time (the others at their current value); the class with most queries is reported.
+    // A class that goes by waves, which know no threshold, is timed so first and then by rows;
+    // it stays unless they are faster by more than 1%
     int64_t q_of[kClasses] = {0, 0, 0, 0};
     for (int32_t r = 0; r < nreq; ++r)
       if (reqs[r].k >= 1 && reqs[r].k <= MKNN_KMAX) q_of[(reqs[r].k + 15) / 16 - 1] += reqs[r].nq;
@@ -887,11 +892,18 @@ mknn_status mknn_batch_plan_tune(mknn_batch_plan *p, const mknn_request *reqs, i
     for (int c = 0; c < kClasses && st == MKNN_OK && e == hipSuccess; ++c) {
       if (!q_of[c]) continue;
       const int32_t keep = p->merge_min[c];
+      const bool keep_rows = p->rows_only[c];
       int32_t bm = keep;
-      float best_ms = INFINITY;
+      float best_ms = INFINITY, wave_ms = INFINITY;
+      p->rows_only[c] = false;
+      st = mknn_batch_plan_run(p, reqs, nreq, stream);
+      if (st == MKNN_OK && (p->last_waves >> c & 1u)) {
+        time_batch(&wave_ms);
+        p->rows_only[c] = true;
+      }
       const int32_t *cv = c == 0 ? cand1 : candS;
       const int ncv = c == 0 ? 3 : 5;
-      for (int t = 0; t < ncv; ++t) {
+      for (int t = 0; t < ncv && st == MKNN_OK && e == hipSuccess; ++t) {
         p->merge_min[c] = cv[t];
         float tm;
         time_batch(&tm);
@@ -901,8 +913,12 @@ mknn_status mknn_batch_plan_tune(mknn_batch_plan *p, const mknn_request *reqs, i
           bm = cv[t];
         }
       }
-      p->merge_min[c] = (st == MKNN_OK && e == hipSuccess) ? bm : keep;
+      const bool done = st == MKNN_OK && e == hipSuccess;
+      p->merge_min[c] = done ? bm : keep;
+      p->rows_only[c] = done ? 1.01f * best_ms < wave_ms && wave_ms < INFINITY : keep_rows;
     }
+    // the outputs by the choices made
+    if (st == MKNN_OK && e == hipSuccess) st = mknn_batch_plan_run(p, reqs, nreq, stream);
     report = p->merge_min[top];
   }
   (void)hipEventDestroy(e0);

@@ -670,12 +670,16 @@ hipError_t timing_mark(hipStream_t s, bool start) {
 // ---------------------------------------------------------------------------------------
 // Launch configuration and the autotuner's table
 //
-// A configuration picks the kernel family (1: one query per lane, 2: 16 lanes per query in
-// lockstep, 3: 16 lanes per query with independently scheduled rows), the number of
-// candidates per chunk from which k <= 16 merges with the network instead of inserting one
-// by one, and the queries per wavefront of the row kernel.  mknn_autotune fills a table
-// keyed by (device, slots per lane S, k == 16 S, log2 n); launches look their key up and
-// fall back to the measured defaults, but for those that the wave and scan kernels take.  Environment variables override all of it (experiments).
+// The rule of launch_rule.h chooses between rows, waves and scan.  A configuration picks the
+// family of a launch by rows (1: one query per lane, 2: 16 lanes per query in lockstep, 3: 16
+// lanes per query with independently scheduled rows), the number of candidates per chunk from
+// which a chunk merges with the network instead of inserting one by one, and the queries per
+// wavefront of the row kernel.  mknn_autotune fills a table keyed by (device, slots per lane S,
+// k == 16 S, log2 n, the rule's choice for the launch that was tuned); a launch looks up the key
+// of its own choice, and a configuration found there answers it, unless it is the built-in one,
+// which leaves the launch to the rule.  MKNN_KERNEL in the environment names the kernel of all
+// launches, MKNN_MERGE_MIN and MKNN_PER_WAVE override the configuration of launches by rows
+// (experiments).
 // ---------------------------------------------------------------------------------------
 static long env_long(const char *name, long dflt) {
   const char *e = getenv(name);
@@ -685,10 +689,18 @@ static long env_long(const char *name, long dflt) {
 // Untuned launches by rows, measured on the 1M torus: one query per row, and the merge network
 // from 8 candidates per chunk on.
 constexpr TuneConfig kDefaultConfig = {3, 8, 4};
+static bool is_default(const TuneConfig &c) {
+  return c.family == kDefaultConfig.family && c.merge_min == kDefaultConfig.merge_min &&
+         c.per_wave == kDefaultConfig.per_wave;
+}
 
 // The rule's choice of kernel, unless MKNN_KERNEL names one.
-static Walk walk_of(const LaunchSize &l) {
+static const char *walk_named() {
   static const char *const v = getenv("MKNN_KERNEL");
+  return v;
+}
+static Walk walk_of(const LaunchSize &l) {
+  const char *const v = walk_named();
   if (v) return v[0] == 'w' ? Walk::kWaves : v[0] == 's' ? Walk::kScan : Walk::kRows;
   return walk_for(l);
 }
@@ -696,11 +708,11 @@ static Walk walk_of(const LaunchSize &l) {
 static std::mutex g_tune_mu;
 static std::map<uint64_t, TuneConfig> g_tune;
 
-static uint64_t tune_key(int dev, int S, bool exact, int64_t n) {
+static uint64_t tune_key(int dev, int S, bool exact, int64_t n, Walk walk) {
   int b = 0;
   while (b < 40 && ((int64_t)1 << (b + 1)) <= n) ++b;
-  return ((uint64_t)(uint32_t)dev << 32) | ((uint64_t)S << 16) | ((uint64_t)(exact ? 1 : 0) << 8) |
-         (uint64_t)b;
+  return ((uint64_t)(uint32_t)dev << 32) | ((uint64_t)walk << 24) | ((uint64_t)S << 16) |
+         ((uint64_t)(exact ? 1 : 0) << 8) | (uint64_t)b;
 }
 
 static TuneConfig env_overrides(TuneConfig c) {
@@ -717,17 +729,21 @@ static TuneConfig env_overrides(TuneConfig c) {
   return c;
 }
 
-TuneConfig config_for(int kmax, bool exact, int64_t n) {
+// The table's configuration for launches that the rule gives to `walk`; the built-in one if there
+// is none.
+static TuneConfig tuned_config(int kmax, bool exact, int64_t n, Walk walk) {
   const int S = (kmax + 15) / 16;
   int dev = 0;
   (void)hipGetDevice(&dev);
-  TuneConfig c = kDefaultConfig;
-  {
-    std::lock_guard<std::mutex> lk(g_tune_mu);
-    auto it = g_tune.find(tune_key(dev, S, exact && kmax == 16 * S, n));
-    if (it != g_tune.end()) c = it->second;
-  }
-  return env_overrides(c);
+  std::lock_guard<std::mutex> lk(g_tune_mu);
+  auto it = g_tune.find(tune_key(dev, S, exact && kmax == 16 * S, n, walk));
+  return it != g_tune.end() ? it->second : kDefaultConfig;
+}
+
+int32_t merge_min_for(int k, int64_t n) {
+  TuneConfig c = tuned_config(k, false, n, Walk::kRows);
+  if (is_default(c)) c = tuned_config(k, false, n, Walk::kWaves);
+  return env_overrides(c).merge_min;
 }
 
 template <int K, bool EXACTK, bool COUNT>
@@ -924,8 +940,18 @@ static mknn_status run_query(const mknn_cloud *c, const float *d_q, int64_t nq, 
   a.cnt_lists = d_cl;
   a.cnt_inserts = d_ci;
   const bool exact = (d_k == nullptr);
+  // the table's configuration or the forced one; the built-in one leaves the launch to the rule
   const LaunchSize size = {nq, kmax, !exact, m, c->dev_n, c->dev_longest};
-  const Walk walk = force || d_ce ? Walk::kRows : walk_of(size);
+  Walk walk = d_ce ? Walk::kRows : walk_of(size);
+  TuneConfig cfg = force ? *force : tuned_config(kmax, exact, c->dev_n, walk);
+  if (!force) cfg = env_overrides(cfg);
+  if (lazy) {
+    // of the tuned kernels only the scheduled rows filter marked ranks
+    if (cfg.family != 3 && walk != Walk::kRows) cfg = kDefaultConfig;
+    cfg.family = 3;
+    cfg.per_wave = 4;
+  }
+  if (!is_default(cfg) && (force || !walk_named())) walk = Walk::kRows;
   void *scratch = nullptr;
   float4 *qs = nullptr;
   mknn_status st = prepare_queries(c, d_q, nq, s,
@@ -934,11 +960,6 @@ static mknn_status run_query(const mknn_cloud *c, const float *d_q, int64_t nq, 
                                    &qs, &scratch, fixed_scratch);
   if (st != MKNN_OK) return st;
   a.qs = qs;
-  TuneConfig cfg = force ? *force : config_for(kmax, exact, c->dev_n);
-  if (lazy) {
-    cfg.family = 3;   // of the tuned kernels only the rows filter marked ranks
-    cfg.per_wave = 4;
-  }
   a.merge_min = cfg.merge_min;
   // the allocation-free entry point records no timing events (they are created on demand)
   hipError_t e = fixed_scratch ? hipSuccess : timing_mark(s, true);
@@ -1245,7 +1266,7 @@ mknn_status mknn_knn_layout(const mknn_cloud *c, int32_t layout, const float *d_
     return st;
   }
   a.qs = qs;
-  a.merge_min = config_for(16, true, c->dev_n).merge_min;
+  a.merge_min = env_overrides(tuned_config(16, true, c->dev_n, Walk::kRows)).merge_min;
   hipError_t e = timing_mark(s, true);
   const int64_t waves = (nq + 3) / 4;
   const dim3 grid((uint32_t)((waves + 3) / 4));
@@ -1374,12 +1395,17 @@ mknn_status mknn_autotune(const mknn_cloud *c, const float *d_q, int64_t nq, int
     if (st != MKNN_OK) return st;
   }
   const int S = (k + 15) / 16;
+  // the built-in configuration is timed as the rule runs it
+  const LaunchSize size = {nq, k, false, m, c->dev_n, c->dev_longest};
+  const Walk walk = walk_of(size);
   std::vector<TuneConfig> cand;
   for (int pw : {4, 8}) {
-    if (S == 1)
-      for (int mm : {4, 6, 8}) cand.push_back({3, mm, pw});
-    else
-      for (int mm : {4, 6, 8, 11}) cand.push_back({3, mm, pw});
+    for (int mm : {4, 6, 8, 11}) {
+      if (S == 1 && mm == 11) continue;
+      // rows that gather know no threshold: one of them, unless the built-in one is by rows
+      if (pw == 4 && gather_rows(k, nq) && (mm == 4 || (mm == 6 && walk == Walk::kRows))) continue;
+      cand.push_back({3, mm, pw});
+    }
   }
   cand.push_back({2, 6, 4});
   cand.push_back({1, 6, 4});
@@ -1418,10 +1444,8 @@ mknn_status mknn_autotune(const mknn_cloud *c, const float *d_q, int64_t nq, int
   // The built-in configuration stays unless a candidate is faster by more than 1%, so that
   // timing noise (a profiler attached, another process on the device) does not flip the
   // choice between near-equal candidates.
-  const TuneConfig def = kDefaultConfig;
   for (size_t t = 0; t < cand.size(); ++t)
-    if (cand[t].family == def.family && cand[t].merge_min == def.merge_min &&
-        cand[t].per_wave == def.per_wave && ms[t] <= 1.01f * ms[bi]) {
+    if (is_default(cand[t]) && ms[t] <= 1.01f * ms[bi]) {
       bi = t;
       break;
     }
@@ -1429,7 +1453,7 @@ mknn_status mknn_autotune(const mknn_cloud *c, const float *d_q, int64_t nq, int
   (void)hipGetDevice(&dev);
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    g_tune[tune_key(dev, S, k == 16 * S, c->dev_n)] = cand[bi];
+    g_tune[tune_key(dev, S, k == 16 * S, c->dev_n, walk)] = cand[bi];
   }
   const int32_t n_out = (int32_t)std::min<size_t>(cand.size(), max_tried > 0 ? (size_t)max_tried : 0);
   for (int32_t t = 0; t < n_out; ++t)
@@ -1444,6 +1468,8 @@ void mknn_tune_reset(void) {
   g_tune.clear();
 }
 
+static const char *const kWalkWord[] = {"", " waves", " scan"};
+
 mknn_status mknn_tune_save(const char *path) {
   clear_error();
   if (!path) return set_error(MKNN_EINVAL, "mknn_tune_save: path is NULL");
@@ -1453,9 +1479,9 @@ mknn_status mknn_tune_save(const char *path) {
   std::lock_guard<std::mutex> lk(g_tune_mu);
   for (const auto &kv : g_tune) {
     const uint64_t key = kv.first;
-    std::fprintf(f, "%u %u %u %u %d %d %d\n", (unsigned)(key >> 32), (unsigned)((key >> 16) & 0xffff),
+    std::fprintf(f, "%u %u %u %u %d %d %d%s\n", (unsigned)(key >> 32), (unsigned)((key >> 16) & 0xff),
                  (unsigned)((key >> 8) & 0xff), (unsigned)(key & 0xff), kv.second.family,
-                 kv.second.merge_min, kv.second.per_wave);
+                 kv.second.merge_min, kv.second.per_wave, kWalkWord[(key >> 24) & 0xff]);
   }
   const bool ok = std::fclose(f) == 0;
   return ok ? MKNN_OK : set_error(MKNN_EINVAL, std::string("mknn_tune_save: write failed: ") + path);
@@ -1480,7 +1506,15 @@ mknn_status mknn_tune_load(const char *path) {
       ok = false;
       break;
     }
-    const uint64_t key = ((uint64_t)dev << 32) | ((uint64_t)S << 16) | ((uint64_t)exact << 8) | bucket;
+    // an entry of launches by waves or scan names them
+    char word[8] = {0};
+    int walk = 0;
+    if (std::fscanf(f, " %7[a-z]", word) == 1) {
+      walk = std::string(word) == "waves" ? 1 : std::string(word) == "scan" ? 2 : 0;
+      ok = walk != 0;
+    }
+    const uint64_t key = ((uint64_t)dev << 32) | ((uint64_t)walk << 24) | ((uint64_t)S << 16) |
+                         ((uint64_t)exact << 8) | bucket;
     table[key] = {fam, mm, pw};
   }
   std::fclose(f);

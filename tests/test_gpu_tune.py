@@ -86,3 +86,87 @@ def test_batch_plan_tune(env):
             torch.cuda.synchronize()
             assert torch.equal(ri, idx) and torch.equal(rd, dist)
         plan.close()
+
+
+# Launches of k = 40 over 40000 points that the rule gives to the rows (a prefix), to the waves and
+# to the scan kernel (long rows of a prefix), the word of their table entries, and the S class
+KINDS = {"rows": (20000, 20000, ""), "waves": (20000, None, " waves"), "scan": (140000, 20000, " scan")}
+
+
+def _best_ms(torch, f, reps=5):
+    best = 1e9
+    for _ in range(reps):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        f()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+@pytest.mark.parametrize("kind", list(KINDS))
+def test_tuned_configuration_is_run(env, kind, tmp_path):
+    """The tuner's entry is for the kind of launch tuned, which it then answers: with one query per
+    lane in the table (3 times as slow at this k and more) such launches slow down, launches of the
+    other kinds do not, and the rows stay the same.  The built-in entry leaves the launch as it was."""
+    torch, oracle, A, W = env
+    k = 40
+    P = W.random_cloud(40000, seed=5, shape="torus").by_rank
+    cl = A.Cloud.build(P).upload()
+    launches = {}
+    for name, (nq, m, _) in KINDS.items():
+        Q = W.uniform_in_box(np.random.default_rng(nq), nq, *W.bbox_expanded(P, 1.1))
+        launches[name] = (Q, torch.from_numpy(Q).cuda(), m)
+    A.tune_reset()
+    ms = {n: _best_ms(torch, lambda: cl.knn(q, k, m)) for n, (_, q, m) in launches.items()}
+    Q, q, m = launches[kind]
+    before = cl.knn(q, k, m)
+    best, tried = A.autotune(cl, q, k, m)
+    builtin = [t for t in tried if (t["family"], t["merge_min"], t["per_wave"]) == ("rows", 8, 4)]
+    lane = [t for t in tried if t["family"] == "lane"]
+    # the built-in configuration is timed as such a launch runs
+    assert len(builtin) == 1 and builtin[0]["ms"] < 1.3 * ms[kind] + 0.01
+    assert len(lane) == 1 and lane[0]["ms"] > 3 * builtin[0]["ms"]
+    path = tmp_path / "tune.txt"
+    A.tune_save(str(path))
+    entry = path.read_text().split("\n")[1]
+    word = KINDS[kind][2]
+    assert entry.endswith(word) and (word or entry[-1].isdigit())
+    # the same key with one query per lane
+    path.write_text("mknn-tune 1\n" + " ".join(entry.split()[:4]) + " 1 6 4" + word + "\n")
+    A.tune_reset()
+    A.tune_load(str(path))
+    for n, (_, qn, mn) in launches.items():
+        now = _best_ms(torch, lambda: cl.knn(qn, k, mn))
+        assert (now > 2 * ms[n]) == (n == kind), (n, now, ms)
+    idx, dist = cl.knn(q, k, m)
+    torch.cuda.synchronize()
+    assert torch.equal(idx, before[0]) and torch.equal(dist, before[1])
+    A.tune_reset()
+    ri, _, rD = oracle.knn_bruteforce(P, Q[:1000], k + 1, m)
+    assert compare_rows(idx.cpu().numpy()[:1000], dist.cpu().numpy()[:1000], ri[:, :k], rD[:, :k],
+                        rD[:, k], P=P, Q=Q[:1000], m=m) <= 2
+
+
+@pytest.mark.parametrize("m", [None, 9000])
+def test_plan_tune_of_a_class_by_waves(env, m):
+    """A class of k > 16 over whole clouds: timed by waves and by rows; results stay the same, for
+    batches in prefixes as well."""
+    torch, oracle, A, W = env
+    P = W.random_cloud(20000, seed=8, shape="ellipsoid").by_rank
+    cl = A.Cloud.build(P).upload()
+    q = torch.from_numpy(W.uniform_in_box(np.random.default_rng(1), 3000, *W.bbox_expanded(P, 1.1))).cuda()
+    items = A.alloc_outputs([(cl, q, k, m) for k in (10, 20, 33, 64)])
+    plan = A.BatchPlan(len(items), len(items) * 3000)
+    assert plan.tune(items) in (4, 6, 8, 5, 11, 14, 17)
+    torch.cuda.synchronize()
+    for mm in (m, None, 5000):
+        rows = A.alloc_outputs([(cl, q, it[2], mm) for it in items])
+        if mm != m:
+            plan.run(rows)
+        for it in (items if mm == m else rows):
+            ri, rd = cl.knn(q, it[2], it[3])
+            torch.cuda.synchronize()
+            assert torch.equal(it[4], ri) and torch.equal(it[5], rd)
+    plan.close()

@@ -50,3 +50,21 @@ def test_missing_table(api, tmp_path):
     with pytest.raises(MknnError) as e:
         api.tune_load(str(tmp_path / "nope.txt"))
     assert e.value.status == ENOTFOUND
+
+
+def test_entries_name_the_kernel_they_are_for(api, tmp_path):
+    """An entry for launches by waves or scan says so; it stands beside the one for rows."""
+    from paper_2605_02224_amd._lib import MknnError, EINVAL
+    src = tmp_path / "in.txt"
+    lines = ["0 2 0 18 3 6 4", "0 2 0 18 1 6 4 waves", "0 2 0 18 3 11 8 scan"]
+    src.write_text("mknn-tune 1\n" + "\n".join(lines) + "\n")
+    api.tune_reset()
+    api.tune_load(str(src))
+    out = tmp_path / "out.txt"
+    api.tune_save(str(out))
+    assert sorted(out.read_text().split("\n")[1:-1]) == sorted(lines)
+    api.tune_reset()
+    src.write_text("mknn-tune 1\n0 2 0 18 3 6 4 rowss\n")
+    with pytest.raises(MknnError) as e:
+        api.tune_load(str(src))
+    assert e.value.status == EINVAL
