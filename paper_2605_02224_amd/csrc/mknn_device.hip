@@ -489,10 +489,15 @@ static mknn_status install_gathered(mknn_cloud *c, int dev, hipStream_t s) {
   c->device = dev;
   const int64_t n = c->n, nnz = (int64_t)c->succ.ent.size();
   Arena m;
-  int64_t *off = nullptr;
   hipError_t e = m.alloc(n, cap);
+  // the lists' offsets and entries wait in the arena's slack, which they fit but for lists of
+  // less than two entries a point
   const size_t off_bytes = sizeof(int64_t) * (size_t)(n + 1);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&off, off_bytes + sizeof(int32_t) * (size_t)nnz + 16, s);
+  const size_t list_bytes = off_bytes + sizeof(int32_t) * (size_t)nnz;
+  void *scratch = nullptr;
+  if (e == hipSuccess && list_bytes > sizeof(float4) * (size_t)(cap - nnz - kEntPad))
+    e = hipMallocAsync(&scratch, list_bytes, s);
+  int64_t *off = scratch ? (int64_t *)scratch : (int64_t *)((float4 *)m.ent + nnz + kEntPad);
   int32_t *succ = (int32_t *)((char *)off + off_bytes);
   if (e == hipSuccess)
     e = hipMemcpyAsync(m.lst, lst.data(), sizeof(uint64_t) * lst.size(), hipMemcpyHostToDevice, s);
@@ -508,7 +513,7 @@ static mknn_status install_gathered(mknn_cloud *c, int dev, hipStream_t s) {
                        off, succ, m.lst, (const float4 *)m.pts, n, nnz, (float4 *)m.ent);
     e = hipGetLastError();
   }
-  if (off) (void)hipFreeAsync(off, s);
+  if (scratch) (void)hipFreeAsync(scratch, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return m.fail(e);
   m.give(c, nnz, longest);

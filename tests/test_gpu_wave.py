@@ -313,3 +313,30 @@ def test_keys_that_agree(env, k):
             # (near-ties, which are all of the sites here, may stand for each other; the rest of
             # the rule holds: true distances, ordered by (D, age), no rank twice)
             compare_rows(idx, dist, ri[:, :k], rD[:, :k], rD[:, k], P=P, Q=Q, m=m)
+
+
+@pytest.mark.parametrize("n", [3, 300, 5000, 90000])
+def test_upload_takes_the_arena_alone(env, n):
+    """An upload needs no device memory beside what the cloud then holds: the stream-ordered pool's
+    high mark does not move."""
+    import ctypes
+    torch, oracle, A, W, _, _ = env
+    hip = A._lib.lib()   # (symbols of the HIP runtime it is linked with)
+    pool, v = ctypes.c_void_p(), ctypes.c_uint64(0)
+    high = 8             # hipMemPoolAttrUsedMemHigh
+    assert hip.hipDeviceGetDefaultMemPool(ctypes.byref(pool), 0) == 0
+    P = np.random.default_rng(n).standard_normal((n, 3)).astype(np.float32)
+    cl = A.Cloud.build(P, device=n > 3000)
+    torch.cuda.synchronize()
+
+    def mark():
+        assert hip.hipMemPoolGetAttribute(pool, high, ctypes.byref(v)) == 0
+        return v.value
+    assert hip.hipMemPoolSetAttribute(pool, high, ctypes.byref(ctypes.c_uint64(0))) == 0
+    before = mark()
+    cl.upload()
+    torch.cuda.synchronize()
+    assert mark() == before
+    Q = P[:40]
+    idx, _ = _rows(torch, cl, Q, 1)
+    assert (idx[:, 0] == np.arange(len(Q))).all()
