@@ -395,14 +395,14 @@ mknn_status pack_lists(mknn_cloud *c, HostPack *p) {
 }
 
 // The arena's records written on the device: 16 lanes per list, the list's entries (CSR) with
-// their points; then the padding.  Bound by the writes, 16 bytes a record.
+// their points; then the padding.  Bound by the writes, 16 bytes a record.  A grid of any size:
+// a launch holds no more than 2^32 threads.
 __global__ __launch_bounds__(256) void gather_records_kernel(const int64_t *off, const int32_t *succ,
                                                              const uint64_t *lst, const float4 *pts,
                                                              int64_t n, int64_t nnz, float4 *ent) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t r = t >> 4;
   const int l = (int)(t & 15);
-  if (r < n) {
+  for (int64_t r = t >> 4; r < n; r += ((int64_t)gridDim.x * blockDim.x) >> 4) {
     const int64_t b = off[r], len = off[r + 1] - b;
     float4 *to = ent + (uint32_t)lst[r];
     for (int64_t i = l; i < len; i += 16) {
@@ -508,8 +508,8 @@ static mknn_status install_gathered(mknn_cloud *c, int dev, hipStream_t s) {
   if (e == hipSuccess && nnz > 0)
     e = hipMemcpyAsync(succ, c->succ.ent.data(), sizeof(int32_t) * (size_t)nnz, hipMemcpyHostToDevice, s);
   if (e == hipSuccess) {
-    const int64_t threads = std::max<int64_t>(16 * n, kEntPad);
-    hipLaunchKernelGGL(gather_records_kernel, dim3((uint32_t)((threads + 255) / 256)), dim3(256), 0, s,
+    const int64_t blocks = std::min<int64_t>((n + 15) / 16, 1 << 20);
+    hipLaunchKernelGGL(gather_records_kernel, dim3((uint32_t)blocks), dim3(256), 0, s,
                        off, succ, m.lst, (const float4 *)m.pts, n, nnz, (float4 *)m.ent);
     e = hipGetLastError();
   }
