@@ -340,3 +340,119 @@ def test_upload_takes_the_arena_alone(env, n):
     Q = P[:40]
     idx, _ = _rows(torch, cl, Q, 1)
     assert (idx[:, 0] == np.arange(len(Q))).all()
+
+
+# Launches of every kernel the rule can choose, above its thresholds: (queries, k, prefix; "var": a k
+# and prefix per query up to these), for a cloud of 4000 points
+ROUTES = {
+    "gathered_k9": (196608, 9, None), "gathered_k16": (196609, 16, None),
+    "gathered_prefix": (196608, 12, 700), "rows_k2": (65537, 2, None), "rows_k8": (70001, 8, None),
+    "rows_k16": (70003, 16, None), "rows_prefix_k3": (6001, 3, 1700), "rows_prefix_k16": (8191, 16, 120),
+    "rows_prefix_k17": (20001, 17, 1500), "rows_prefix_k33": (20002, 33, 1500),
+    "rows_prefix_k64": (20003, 64, 1500), "rows_one_site_more": (20001, 64, 65),
+    "rows_as_many": (20001, 32, 32), "waves_k20": (70001, 20, None), "waves_k64": (131073, 64, None),
+    "waves_one_site_more": (3001, 64, 65), "waves_k1": (70001, 1, None), "scan_k33": (65537, 33, 1500),
+    "scan_k64": (65538, 64, 66), "scan_k20": (262144, 20, 900), "scan_one_site_more": (262145, 32, 33),
+    "var_waves": (70001, 32, "var"), "var_scan_32": (98305, 32, "var"), "var_scan_64": (100001, 64, "var"),
+    "var_rows": (131073, 16, "var"), "var_rows_k4": (262145, 4, "var"),
+}
+
+
+@pytest.mark.parametrize("shape", ["torus", "lattice"])
+@pytest.mark.parametrize("route", list(ROUTES))
+def test_routes_against_brute_force(env, route, shape):
+    """Sampled rows of large launches: ranks equal the FP64 brute force's; on the lattice, where whole
+    shells tie, by (D, age) exactly."""
+    torch, oracle, A, W, P, cl = env
+    if shape == "lattice":
+        P, cl = _lattice(A, 16, 3)
+    n = len(P)
+    nq, k, m = ROUTES[route]
+    rng = np.random.default_rng(nq + k)
+    Q = W.uniform_in_box(rng, nq, *W.bbox_expanded(P, 1.1))
+    if shape == "lattice":
+        Q = (np.round(2 * Q) / 2).astype(np.float32)
+    q = torch.from_numpy(Q).cuda()
+    pick = np.sort(rng.choice(nq, 400, replace=False))
+    if m == "var":
+        kq = rng.integers(1, k + 1, nq).astype(np.int32)
+        kq[0] = k
+        mq = np.exp(rng.uniform(0, np.log(n), nq)).astype(np.int32).clip(1, n)
+        mq[rng.random(nq) < 0.3] = n
+        idx, dist, off = cl.knn_var(q, torch.from_numpy(kq).cuda(), torch.from_numpy(mq).cuda())
+        torch.cuda.synchronize()
+        off = off.cpu().numpy()
+        rows = [(i, int(kq[i]), int(mq[i])) for i in pick]
+        idx, dist = idx.cpu().numpy(), dist.cpu().numpy()
+        got = [(idx[off[i]:off[i] + kk], dist[off[i]:off[i] + kk]) for i, kk, _ in rows]
+    else:
+        idx, dist = _rows(torch, cl, Q, k, m)
+        rows = [(i, k, m or n) for i in pick]
+        got = [(idx[i], dist[i]) for i in pick]
+    ex = 0
+    for (i, kk, mm), (gi, gd) in zip(rows, got):
+        D = ((Q[i].astype(np.float64) - P[:mm].astype(np.float64)) ** 2)
+        D = D[:, 0] + D[:, 1] + D[:, 2]
+        order = np.argsort(D, kind="stable")[:kk]
+        ri = np.full(kk, -1)
+        ri[:len(order)] = order
+        rD = np.full(kk, np.inf)
+        rD[:len(order)] = D[order]
+        if shape == "lattice":
+            assert np.array_equal(gi, ri), (i, kk, mm)
+        else:
+            ex += compare_rows(gi[None], gd[None], ri[None], rD[None], P=P, Q=Q[i:i + 1], m=mm)
+    assert ex <= 2
+
+
+@pytest.mark.parametrize("nq,k,m", [(20001, 8, 2500), (20002, 30, 2500), (20003, 47, 2500),
+                                    (70001, 16, None), (262144, 12, 2500), (3001, 40, None)])
+def test_pending_deletions_on_every_route(env, nq, k, m):
+    """Rows filtered by pending deletions, by the row, wave and scan kernels (k + 16 neighbours
+    walked for), and per query; against the brute force over what is left."""
+    torch, oracle, A, W, P, _ = env
+    n = len(P)
+    cl = A.Cloud.build(P).upload()
+    rng = np.random.default_rng(nq)
+    gone = rng.choice(np.arange(1, n), 40, replace=False).astype(np.int32)
+    cl.delete_lazy(gone)
+    live = np.ones(n, np.uint8)
+    live[gone] = 0
+    Q = W.uniform_in_box(rng, nq, *W.bbox_expanded(P, 1.1))
+    pick = np.sort(rng.choice(nq, 500, replace=False))
+    idx, dist = _rows(torch, cl, Q, k, m)
+    assert cl.pending_deletes == len(gone)
+    ri, _, rD = oracle.knn_bruteforce(P, Q[pick], k, m, live=live)
+    assert compare_rows(idx[pick], dist[pick], ri, rD, P=P, Q=Q[pick], m=m, live=live) <= 2
+    kq = rng.integers(1, k + 1, nq).astype(np.int32)
+    mq = rng.integers(1, n + 1, nq).astype(np.int32)
+    idx, dist, off = cl.knn_var(torch.from_numpy(Q).cuda(), torch.from_numpy(kq).cuda(),
+                                torch.from_numpy(mq).cuda())
+    torch.cuda.synchronize()
+    idx, dist, off = idx.cpu().numpy(), dist.cpu().numpy(), off.cpu().numpy()
+    ex = 0
+    for i in pick[:80]:
+        ri, _, rD = oracle.knn_bruteforce(P, Q[i:i + 1], int(kq[i]), int(mq[i]), live=live)
+        ex += compare_rows(idx[None, off[i]:off[i + 1]], dist[None, off[i]:off[i + 1]], ri, rD, P=P,
+                           Q=Q[i:i + 1], m=int(mq[i]), live=live)
+    assert ex <= 2
+
+
+def test_not_a_number_by_every_kernel(env):
+    """NaN queries, nearer to nothing, get at most the site that their descent starts from (the rows
+    may drop it, which order it behind nothing), and leave the other queries of their wavefront
+    alone."""
+    torch, oracle, A, W, P, cl = env
+    for nq, k, m in ((64, 1, None), (64, 16, None), (70001, 1, None), (70001, 8, None), (70001, 20, None),
+                     (196608, 12, None), (65537, 40, 1500), (20001, 20, 1500)):
+        Q = W.uniform_in_box(np.random.default_rng(nq + k), nq, *W.bbox_expanded(P, 1.1))
+        want, _ = _rows(torch, cl, Q, k, m)
+        at = np.arange(5, nq, 97)
+        B = Q.copy()
+        B[at, at % 3] = np.nan
+        idx, dist = _rows(torch, cl, B, k, m)
+        assert np.isin(idx[at], (0, -1)).all() and ((idx[at] == 0).sum(1) <= 1).all(), (nq, k)
+        assert np.isnan(dist[at][idx[at] == 0]).all() and np.isinf(dist[at][idx[at] == -1]).all(), (nq, k)
+        keep = np.ones(nq, bool)
+        keep[at] = False
+        assert np.array_equal(idx[keep], want[keep]), (nq, k)
