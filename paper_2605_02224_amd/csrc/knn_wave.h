@@ -338,18 +338,15 @@ __device__ __forceinline__ float4 ring_site(const QueryArgs &a, uint32_t e) {
   return e == kHeadRecord ? make_float4(a.hx, a.hy, a.hz, __int_as_float(a.head)) : a.ent[e];
 }
 
-// N holds the 64 smallest keys of `before` and of the new keys `x`, and keys that fell out agree
-// with the k-th in their upper bits (they are <= thr): N with the nearest of those that agree,
-// by their exact keys.  At k = 64 every key that falls out next to one like it comes here, a few
+// Some of the keys `lost`, which fell out of the full N, agree with the k-th in their upper bits
+// (they are <= thr): N with the nearest of those that agree, by their exact keys.  At k = 64 every key that falls out next to one like it comes here, a few
 // in a hundred queries of most clouds and several in each where a query is far from all points
 // or amid a shell; answering those again with exact keys, as before, took as long as the rest:
 // 4096 queries of k=64 over 400k points 129 us, now 60, 200k over 200k points with far outliers 51
 // ms, now 18.5.
 template <int DW, int R>
-__device__ __forceinline__ uint32_t keep_nearest(WaveLds<DW, R> &w, uint32_t N, uint32_t before,
-                                                 uint32_t x, uint32_t thr, int lane) {
-  x = merge_rows(sort_rows(x, lane), lane);
-  const uint32_t lost = max(before, lane_value(x, 63 - lane));
+__device__ __forceinline__ uint32_t keep_nearest(WaveLds<DW, R> &w, uint32_t N, uint32_t lost,
+                                                 uint32_t thr, int lane) {
   uint64_t out = lanes_where(lost <= thr);
   while (out) {
     const uint32_t o = readlane_u32(lost, pop_lane(out));
@@ -420,7 +417,8 @@ __device__ __forceinline__ bool expand(const QueryArgs &a, WaveLds<DW, R> &w, co
     if (!(open | pend)) break;
     uint32_t u;
     uint64_t cand;
-    const uint64_t runs = pend & lanes_where(plen >= 64);
+    // (a prefix, cap = 24, ends most lists soon)
+    const uint64_t runs = pend & lanes_where(plen >= (cap == 64u ? 64u : 256u));
     if (runs) {
       // what is left of a long list is read on by itself, 64 entries a step: neither the
       // descriptors of the sites behind it are loaded nor a layout made (200k points with 20
@@ -531,16 +529,16 @@ __device__ __forceinline__ bool expand(const QueryArgs &a, WaveLds<DW, R> &w, co
     nslot += nc;
     wave_lds_sync();
     // ---- insert
-    const uint32_t before = N;
-    const uint64_t added = fresh;
-    uint32_t lost = kPadKey;   // keys that fall out of the lanes
+    uint32_t lost = kPadKey;   // keys that fall out of the lanes, in any
     if (nc <= kWaveInsert) {
       // one by one: every position keeps the middle of its key, the one before and the new.
-      // The last lane may fill up within these keys, so each may push one out (an empty
+      // Once the last lane is full, within these keys or before, each pushes one out (an empty
       // lane's key is above every threshold)
+      int left = nc;
       do {
         const uint32_t nk = readlane_u32(key, pop_lane(fresh));
-        lost = min(lost, max(readlane_u32(N, 63), nk));
+        --left;
+        if (nreal + nc > 64) lost = writelane_u32(max(readlane_u32(N, 63), nk), left, lost);
         N = median(wave_shr1(N), nk, N);
       } while (fresh);
     } else {
@@ -562,8 +560,8 @@ __device__ __forceinline__ bool expand(const QueryArgs &a, WaveLds<DW, R> &w, co
     }
     nreal = min(64, nreal + nc);
     thr = min(readlane_u32(N, q.k - 1) | kTieBits, kMaxKey);
-    if (nreal == 64 && lanes_where(lost <= thr)) {   // agrees with the k-th
-      N = keep_nearest(w, N, before, in_mask(added) ? key : kPadKey, thr, lane);
+    if (__builtin_expect(nreal == 64 && lanes_where(lost <= thr) != 0, 0)) {   // agrees with the k-th
+      N = keep_nearest(w, N, lost, thr, lane);
       thr = min(readlane_u32(N, q.k - 1) | kTieBits, kMaxKey);
     }
   }

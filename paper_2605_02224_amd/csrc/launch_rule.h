@@ -29,21 +29,17 @@ constexpr int64_t kWaveSortQueries = 262144;
 
 // ---- Clouds with long lists.  Most clouds' longest lists grow slowly (torus, sphere, solid: 140
 // entries at 3k points, 500 at 1M); sheets, whose hull meets their rim, have some of 1000 to
-// 9000 (height fields of 300k to 1M points), and a point far from the others, or inside a
-// closed surface, is adjacent to a large part of the cloud (20 outliers of 200k points: 53551).
-// Queries that come to such a list read it to its end, which a wavefront's other queries wait
-// for.
+// 12000 (height fields of 100k to 1M points, up to n / 32), and a point far from the others, or
+// inside a closed surface, is adjacent to a large part of the cloud (20 outliers of 200k points:
+// 53551).  Queries that come to such a list read it to its end, which a wavefront's other
+// queries wait for.
 constexpr int64_t kLongList = 1024;
 inline bool long_lists(const LaunchSize &l) { return l.longest > kLongList; }
 // Some list is a good part of the cloud: many queries meet it, and the row kernel's four
 // queries side by side read it together.
 inline bool hub_lists(const LaunchSize &l) {
-  return l.longest > 4096 && l.longest > l.n / 64;
+  return l.longest > 4096 && l.longest > l.n / 16;
 }
-
-// Single neighbours with a hub, by waves, are bucketed from here on, and by rows before (20000
-// queries of the sphere and its centre below: rows 362 us, waves as they come 393).
-constexpr int64_t kHubSortQueries = 32768;
 
 // Rows or wavefronts.  The wave kernel's steps are short (a query's critical path is half the
 // row kernel's), the row kernel's lanes are fuller for short rows of many queries.  us per
@@ -61,7 +57,7 @@ constexpr int64_t kHubSortQueries = 32768;
 // 576; 500k queries k=16 680 / 1139 / 866, k=20 1067 / 1337 / 986, k=64 3622 / 3724 / 2447; 20000
 // queries k=32 131 / 148 / 206; 4096 queries k=16 50 / 39 / 52.  A k and prefix per query
 // (prefixes of 400 to 400k; all 400k): 20000 queries k <= 32 236 / 207 / 207 (250 / 184 / 218);
-// 70000 k <= 32 402 / 364 / 367 (414 / 309 / 399); 131072 k <= 16 375 / 375 / 354 (395 / 350 / 399),
+// 70000 k <= 32 402 / 364 / 367 (414 / 309 / 399), k <= 64 scan 474, waves 528; 131072 k <= 16 375 / 375 / 354 (395 / 350 / 399),
 // k <= 32 533 / 513 / 462 (568 / 439 / 512); 200000 k <= 4 333 / 333 / 326 (358 / 362 / 373), k <= 16
 // 458 / 487 / 454 (498 / 457 / 524); 262144 k <= 4, bucketed 370 / 417 / 411 (408 / 422 / 447); 500k
 // queries k <= 16 878 / 983 / 890 (944 / 871 / 965), k <= 32 1414 / 1418 / 1147 (1464 / 1145 / 1243).
@@ -77,7 +73,7 @@ constexpr int64_t kHubSortQueries = 32768;
 inline Walk walk_for(const LaunchSize &l) {
   if (hub_lists(l) && l.nq > 8192) {
     if (l.per_query) return Walk::kRows;
-    if (l.kmax == 1) return l.nq > kSmallQueries && l.nq < kHubSortQueries ? Walk::kRows : Walk::kWaves;
+    if (l.kmax == 1) return Walk::kWaves;
     return l.kmax <= 16 && l.m >= l.n && l.nq <= kLargeQueries ? Walk::kWaves : Walk::kRows;
   }
   const bool uniform = !l.per_query, prefix = uniform && l.m < l.n;
@@ -86,12 +82,12 @@ inline Walk walk_for(const LaunchSize &l) {
     // wavefront and not bucketed either, issue less
     if (l.nq > 4096 && l.nq < kSortMinQueries && (l.kmax <= 4 || (l.kmax <= 16 && l.m < l.n / 32)))
       return Walk::kRows;
-    if (l.nq > 13312 && l.kmax > 16 && l.nq <= kSmallQueries) return Walk::kRows;
+    if (l.nq > 15360 && l.kmax > 16 && l.nq <= kSmallQueries) return Walk::kRows;
   }
   if (l.nq <= kSmallQueries || (uniform && l.kmax == 1)) return Walk::kWaves;
   if (!uniform) {
     if (l.nq <= kLargeQueries || (long_lists(l) && l.nq < kWaveSortQueries)) return Walk::kWaves;
-    if (l.kmax > 16) return l.nq <= 98304 ? Walk::kWaves : Walk::kScan;
+    if (l.kmax > 16) return l.kmax <= 32 && l.nq <= 98304 ? Walk::kWaves : Walk::kScan;
     // (bucketing costs what the waves gain from it)
     return l.nq < (l.kmax <= 4 ? kWaveSortQueries : 131073) ? Walk::kWaves : Walk::kRows;
   }
@@ -106,7 +102,7 @@ inline Walk walk_for(const LaunchSize &l) {
 // hub earlier: the descents that end in its list then share their wavefronts (sphere and centre,
 // 200k queries 1270 us as they come, 552 bucketed).
 inline int64_t wave_sort_min(const LaunchSize &l, bool planes) {
-  if (l.kmax == 1 && hub_lists(l)) return kHubSortQueries;
+  if (l.kmax == 1 && hub_lists(l)) return 32768;
   return l.kmax > 32 || planes ? kWaveSortQueries / 2 : kWaveSortQueries;
 }
 
@@ -119,16 +115,17 @@ constexpr bool gather_rows(int32_t k, int64_t nq) { return k > 8 && nq >= 196608
 
 // How the wave kernel lays the queries out: lanes per query in the descent, and queries per
 // wavefront (at most 64 / lanes; a second one only once every resident wavefront has one).
-// Eight queries a wavefront pay for single neighbours and for bucketed launches, 8 lanes / 16,
-// us: 65536 queries over a 400k-point torus k=1 45 / 54, k=20 187 / 181, k=32 255 / 243; 500k
-// over a solid of 5M k=20 1240 / 1290; and not where lists are long (height field, 65536 queries
+// Eight queries a wavefront pay for short rows and for bucketed launches, 8 lanes / 16, us: 65536
+// queries over a 400k-point torus k=1 45 / 54, k=4 97 / 101, k=20 187 / 181, k=32 255 / 243 (with a
+// k and prefix each k <= 4 212 / 198); 500k over a solid of 5M k=20 1240 / 1290; and not where lists are long (height field, 65536 queries
 // k=1 219 / 149, 300k of k=20 1410 / 1140).
 struct WaveShape {
   int32_t lanes, per_wave;
 };
 inline WaveShape wave_shape(const LaunchSize &l, int64_t resident) {
   WaveShape w;
-  const bool eight = l.kmax == 1 || (l.kmax <= 32 && l.nq >= kWaveSortQueries);
+  const bool eight =
+      l.kmax <= (l.per_query ? 1 : 8) || (l.kmax <= 32 && l.nq >= kWaveSortQueries);
   w.lanes = eight && !long_lists(l) && l.nq >= 8 * resident ? 8 : 16;
   w.per_wave = 1;
   // a single neighbour has no expansion to wait for: four descents side by side as soon as they

@@ -353,7 +353,7 @@ ROUTES = {
     "rows_as_many": (20001, 32, 32), "waves_k20": (70001, 20, None), "waves_k64": (131073, 64, None),
     "waves_one_site_more": (3001, 64, 65), "waves_k1": (70001, 1, None), "scan_k33": (65537, 33, 1500),
     "scan_k64": (65538, 64, 66), "scan_k20": (262144, 20, 900), "scan_one_site_more": (262145, 32, 33),
-    "var_waves": (70001, 32, "var"), "var_scan_32": (98305, 32, "var"), "var_scan_64": (100001, 64, "var"),
+    "var_waves": (70001, 32, "var"), "var_scan_32": (98305, 32, "var"), "var_scan_64": (70002, 64, "var"),
     "var_rows": (131073, 16, "var"), "var_rows_k4": (262145, 4, "var"),
 }
 

@@ -54,8 +54,10 @@ def test_hubs(rule):
                                  for k in (4, 32)])] == ["rows"] * 6
     assert [a[0] for a in rule(*[dict(nq=nq, k=32, m=20000, **hub) for nq in (10000, 70000, 500000)])] == ["rows"] * 3
     assert rule(dict(nq=200000, k=1, **hub)) == [("waves", 1, 16, 4)]
-    assert [a[:2] for a in rule(*[dict(nq=nq, k=1, **hub) for nq in (16384, 16385, 32767, 32768)])] == [
-        ("waves", 0), ("rows", 0), ("rows", 0), ("waves", 1)]
+    # (a sheet's longest list, n / 32, is none)
+    assert rule(dict(nq=200000, k=32, n=400000, longest=12366)) == [("waves", 0, 16, 4)]
+    assert [a[:2] for a in rule(*[dict(nq=nq, k=1, **hub) for nq in (16385, 32767, 32768)])] == [
+        ("waves", 0), ("waves", 0), ("waves", 1)]
 
 
 def test_long_lists(rule):
@@ -72,12 +74,12 @@ def test_few_queries_in_prefixes(rule):
     """One short query to a wavefront, or just over a whole round of wavefronts: rows where a prefix
     leaves the waves' batches half empty; four descents to a wavefront for single neighbours."""
     ask = [dict(nq=nq, k=k, m=m) for nq, k, m in (
-        (4097, 2, 100000), (8191, 4, 200000), (8191, 16, 12000), (5000, 8, 4000), (13313, 17, 100000),
+        (4097, 2, 100000), (8191, 4, 200000), (8191, 16, 12000), (5000, 8, 4000), (15361, 17, 100000),
         (16384, 64, 399999))]
     assert [a[0] for a in rule(*ask)] == ["rows"] * 6
     ask = [dict(nq=nq, k=k, m=m) for nq, k, m in (
         (4096, 2, 100000), (8192, 4, 200000), (8191, 16, 13000), (8191, 5, 100000), (8191, 17, 4000),
-        (13312, 64, 100000), (16384, 16, 100000), (8191, 1, 4000), (8191, 2, 400000), (16384, 64, 400000))]
+        (15360, 64, 100000), (16384, 16, 100000), (8191, 1, 4000), (8191, 2, 400000), (16384, 64, 400000))]
     assert [a[0] for a in rule(*ask)] == ["waves"] * 10
     assert rule(*[dict(nq=nq, k=1) for nq in (3072, 3073, 8191, 16384, 65535, 65536)]) == [
         ("waves", 0, 16, 1), ("waves", 0, 16, 4), ("waves", 0, 16, 4), ("waves", 0, 16, 4),
@@ -88,9 +90,9 @@ def test_a_k_and_prefix_per_query(rule):
     """Waves while they are not bucketed, the scan kernel only for long rows of many queries, rows
     for short rows of many."""
     ask = [dict(nq=nq, k=k, var=1) for nq, k in (
-        (65536, 64), (65537, 32), (98304, 17), (131072, 16), (262143, 4), (262143, 1))]
-    assert [a[0] for a in rule(*ask)] == ["waves"] * 6
+        (65536, 64), (65537, 32), (98304, 32), (98304, 17), (131072, 16), (262143, 4), (262143, 1))]
+    assert [a[0] for a in rule(*ask)] == ["waves"] * 7
     assert [a[0] for a in rule(*[dict(nq=nq, k=k, var=1) for nq, k in (
-        (98305, 17), (131072, 64), (1000000, 32))])] == ["scan"] * 3
+        (98305, 17), (65537, 33), (131072, 64), (1000000, 32))])] == ["scan"] * 4
     assert [a[0] for a in rule(*[dict(nq=nq, k=k, var=1) for nq, k in (
         (131073, 5), (262144, 16), (262144, 2), (262144, 1), (1000000, 8))])] == ["rows"] * 5
