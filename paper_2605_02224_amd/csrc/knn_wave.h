@@ -1,8 +1,9 @@
 // The query kernels' walk: descents side by side, expansions one query per wavefront.
 //
-// What bounds the walk is the issue of instructions, vector and scalar alike (0.9 ms per 1e9 of
-// them; its lists sit in the caches), so the split follows where each part keeps the 64 lanes
-// busy:
+// What bounds the expansions is the issue of instructions, vector and scalar alike (1M queries
+// of k=64: 5.93e9 in 5.15 ms; the lists sit in the caches), so the split follows where each part
+// keeps the 64 lanes busy.  Descents alone wait for their chains of loads (k=1: 0.30e9 in 0.48
+// ms, wavefronts waiting for 70% of it).
 //
 //   descent (Alg. 1): DW lanes per query, 64 / DW queries of a wavefront side by side.  A
 //     step reads DW consecutive entries of a row's current list; the first strictly closer
@@ -31,10 +32,10 @@
 //     decides by the exact keys, which are still in their slots, which of them stay.
 // Sites already offered are recognised by rank in an open-addressed table in LDS.
 //
-// Measured, against the row kernel: 2000 queries of k=20 26 us for 63; 200k of k=64 1.33 ms for
-// 1.86; 500k of k=1 0.55 ms for 0.69; 150k of k=32 with pending deletions 0.59 ms for 0.86.  1M
-// queries of k=16 issue 1970 instructions a query (757 vector, 796 scalar, 213 branches) in
-// 1.86 ms, the row kernel 2050 in 1.89.
+// Measured, against the row kernel: 2000 queries of k=20 over 1M points 30 us for 77; 200k of
+// k=64 over 200k points 1.05 ms for 1.55; 500k of k=1 0.245 ms for 0.31; 131k of k=32 with pending
+// deletions 0.60 ms for 0.86; 1M queries of k=16 over 1M points 1.96 ms for 1.75 (the row kernel
+// gathers candidates there).
 #pragma once
 #include "knn_group.h"
 
@@ -339,11 +340,11 @@ __device__ __forceinline__ float4 ring_site(const QueryArgs &a, uint32_t e) {
 }
 
 // Some of the keys `lost`, which fell out of the full N, agree with the k-th in their upper bits
-// (they are <= thr): N with the nearest of those that agree, by their exact keys.  At k = 64 every key that falls out next to one like it comes here, a few
-// in a hundred queries of most clouds and several in each where a query is far from all points
-// or amid a shell; answering those again with exact keys, as before, took as long as the rest:
-// 4096 queries of k=64 over 400k points 129 us, now 60, 200k over 200k points with far outliers 51
-// ms, now 18.5.
+// (they are <= thr): N with the nearest of those that agree, by their exact keys.  At k = 64 every
+// key that falls out next to one like it comes here, a few in a hundred queries of most clouds
+// and several in each where a query is far from all points or amid a shell; answering those
+// again with exact keys throughout took as long as the rest (4096 queries of k=64 over 400k
+// points 129 us, settled here 60).
 template <int DW, int R>
 __device__ __forceinline__ uint32_t keep_nearest(WaveLds<DW, R> &w, uint32_t N, uint32_t lost,
                                                  uint32_t thr, int lane) {

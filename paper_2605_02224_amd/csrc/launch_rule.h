@@ -21,10 +21,12 @@ constexpr int64_t kSortMinQueries = 8192;
 // Sizes between which walk_for() chooses.
 constexpr int64_t kSmallQueries = 16384, kLargeQueries = 65536;
 // The wave kernel gains less from neighbours in a wavefront than the bucketing costs (five
-// launches, 20 us and up) until launches are larger: 1M-point torus, k = 16, 65536 queries 182
-// us as they come, 215 us bucketed; 262144 queries 594 and 590; 1000000 queries 2081 and 1928.
-// With long rows, or the plane fit's gather of their points, it pays from half as many: 200k
-// queries over 200k points, k = 64 1.42 and 1.33 ms, k = 20 with planes 714 and 692 us.
+// launches, 20 us and up) until launches are larger: 1M-point torus, k = 16, 65536 queries 176
+// us as they come, 200 us bucketed; 262144 queries 608 and 604; 1000000 queries 2100 and 1943.
+// With long rows, or the plane fit's gather of their points, it is ahead from about 150k on, by
+// a few per cent, and costs nothing from half kWaveSortQueries on: 200k points, 131072 queries
+// k = 64 718 and 716 us, k = 20 with planes 412 and 415; 160000 876 and 863, 494 and 489; 262144
+// 1360 and 1317, 776 and 758.
 constexpr int64_t kWaveSortQueries = 262144;
 
 // ---- Clouds with long lists.  Most clouds' longest lists grow slowly (torus, sphere, solid: 140
@@ -43,28 +45,34 @@ inline bool hub_lists(const LaunchSize &l) {
 
 // Rows or wavefronts.  The wave kernel's steps are short (a query's critical path is half the
 // row kernel's), the row kernel's lanes are fuller for short rows of many queries.  us per
-// launch over a 1M-point torus, rows (bucketed) / wave (bucketed from kWaveSortQueries on):
+// launch over a 1M-point torus, rows (bucketed; k = 16 gathering from 196608 on) / wave (bucketed
+// from kWaveSortQueries on, k = 64 from half):
 //   queries      k=1         k=8          k=16         k=20         k=32         k=64
-//   10000       51 / 26     69 / 43      89 / 52     111 / 58     140 / 72     248 / 168
-//   32768       51 / 34     90 / 77     122 / 102    152 / 114    195 / 152    375 / 327
-//   65536       76 / 50    136 / 134    188 / 182    241 / 207    312 / 277    633 / 525
-//   98304      101 / 81    182 / 200    255 / 268    328 / 305    433 / 407    899 / 708
-//   262144     213 / 172   397 / 430    567 / 590    730 / 676    990 / 917   2071 / 1591
-//   1000000    695 / 534  1388 / 1433  1947 / 1928  2507 / 2199  3373 / 2974  7195 / 5374
+//   10000       47 / 27     74 / 43      95 / 55     117 / 60     147 / 72     258 / 111
+//   32768       50 / 33     88 / 73     118 / 98     148 / 110    192 / 147    396 / 258
+//   65536       81 / 51    144 / 137    199 / 175    250 / 196    338 / 260    678 / 444
+//   98304      107 / 86    199 / 202    272 / 249    342 / 279    469 / 370    950 / 626
+//   262144     221 / 176   422 / 448    541 / 611    781 / 708   1042 / 948   2129 / 1526
+//   1000000    739 / 541  1412 / 1431  1746 / 1959  2518 / 2232  3387 / 3015  7240 / 5171
+// (Between kLargeQueries and 196608 the two are within 10% for k of 8 to 16, either way by cloud.)
 // Prefixes cut lists short, which leaves the wave kernel's batches half empty; the scan kernel
 // drops a list where the prefix ends, and the rows lose least.  Over 400k points, rows / wave /
-// scan, prefix of 100k: 65536 queries k=8 114 / 145 / 133, k=32 268 / 352 / 297, k=64 579 / 720 /
-// 576; 500k queries k=16 680 / 1139 / 866, k=20 1067 / 1337 / 986, k=64 3622 / 3724 / 2447; 20000
-// queries k=32 131 / 148 / 206; 4096 queries k=16 50 / 39 / 52.  A k and prefix per query
-// (prefixes of 400 to 400k; all 400k): 20000 queries k <= 32 236 / 207 / 207 (250 / 184 / 218);
-// 70000 k <= 32 402 / 364 / 367 (414 / 309 / 399), k <= 64 scan 474, waves 528; 131072 k <= 16 375 / 375 / 354 (395 / 350 / 399),
-// k <= 32 533 / 513 / 462 (568 / 439 / 512); 200000 k <= 4 333 / 333 / 326 (358 / 362 / 373), k <= 16
-// 458 / 487 / 454 (498 / 457 / 524); 262144 k <= 4, bucketed 370 / 417 / 411 (408 / 422 / 447); 500k
-// queries k <= 16 878 / 983 / 890 (944 / 871 / 965), k <= 32 1414 / 1418 / 1147 (1464 / 1145 / 1243).
+// scan, prefix of 100k: 65536 queries k=8 115 / 147 / 133, k=32 270 / 320 / 296, k=64 603 / 613 /
+// 574; 500k queries k=16 694 / 1167 / 865, k=20 1078 / 1359 / 1031, k=64 3635 / 3655 / 2558; 20000
+// queries k=32 130 / 141 / 142; 4096 queries k=16 51 / 37 / 50.  A k and prefix per query
+// (prefixes of 400 to 400k; all 400k): 20000 queries k <= 32 229 / 209 / 201 (238 / 184 / 234);
+// 70000 k <= 32 404 / 348 / 321 (415 / 300 / 350), k <= 64 764 / 554 / 488 (786 / 409 / 518);
+// 131072 k <= 16 369 / 363 / 345 (395 / 340 / 383), k <= 32 538 / 496 / 448 (550 / 427 / 491);
+// 200000 k <= 4 331 / 322 / 317 (367 / 343 / 367), k <= 16 464 / 476 / 444 (503 / 453 / 514);
+// 262144 k <= 4, bucketed 379 / 428 / 417 (417 / 434 / 454); 500k queries k <= 16 856 / 973 / 883
+// (927 / 870 / 957), k <= 32 1399 / 1434 / 1153 (1449 / 1150 / 1231).
 // Few queries in a prefix, rows / waves, over 400k points on a torus and in a solid: 6500 queries
-// k=2, m=100k 17.9 / 21.3 and 18.5 / 20.8, k=4, m=24k 19.5 / 21.6 and 20.7 / 23.6; 8191 queries
-// k=8, m=4k 24 / 26 and 25 / 29; 16384 queries k=32, m=100k 124 / 106 and 123 / 138, k=64 246 / 195
-// and 240 / 267 (13000 queries: waves are ahead in both).
+// k=2, m=100k 18.0 / 22.0 and 19.5 / 21.4, k=4, m=24k 19.3 / 22.7 and 19.8 / 24.6; 8191 queries
+// k=8, m=4k 23.9 / 28.7 and 22.7 / 27.0.  Close to kSmallQueries with long rows a few slow queries
+// hold the waves up, depending on the draw, which bucketed rows share: 16384 queries k=32, m=100k
+// 122 / 149 near a torus, 123 / 110 in its box, 118 / 115 in a solid, m=20k 104 / 117; k=64
+// 249 / 304, 245 / 201, 238 / 239.  In most of the cloud (m=390k) waves are ahead: 127 / 93,
+// 144 / 98.
 // Long lists: 200k queries with a k and prefix each over a height field (longest list 2755), all
 // 400k points: k <= 32 rows 1094, waves 912, scan 1073; k <= 4 563 / 526 / 695.  With a hub, larger
 // launches go by rows but for k = 1, and for k <= 16 up to kLargeQueries: a sphere and its centre
@@ -82,7 +90,7 @@ inline Walk walk_for(const LaunchSize &l) {
     // wavefront and not bucketed either, issue less
     if (l.nq > 4096 && l.nq < kSortMinQueries && (l.kmax <= 4 || (l.kmax <= 16 && l.m < l.n / 32)))
       return Walk::kRows;
-    if (l.nq > 15360 && l.kmax > 16 && l.nq <= kSmallQueries) return Walk::kRows;
+    if (l.nq > 15360 && l.nq <= kSmallQueries && l.kmax > 16 && l.m <= l.n / 2) return Walk::kRows;
   }
   if (l.nq <= kSmallQueries || (uniform && l.kmax == 1)) return Walk::kWaves;
   if (!uniform) {
@@ -115,10 +123,11 @@ constexpr bool gather_rows(int32_t k, int64_t nq) { return k > 8 && nq >= 196608
 
 // How the wave kernel lays the queries out: lanes per query in the descent, and queries per
 // wavefront (at most 64 / lanes; a second one only once every resident wavefront has one).
-// Eight queries a wavefront pay for short rows and for bucketed launches, 8 lanes / 16, us: 65536
-// queries over a 400k-point torus k=1 45 / 54, k=4 97 / 101, k=20 187 / 181, k=32 255 / 243 (with a
-// k and prefix each k <= 4 212 / 198); 500k over a solid of 5M k=20 1240 / 1290; and not where lists are long (height field, 65536 queries
-// k=1 219 / 149, 300k of k=20 1410 / 1140).
+// Eight queries a wavefront pay for short rows, and for bucketed launches over clouds past the
+// caches, 8 lanes / 16, us: 65536 queries over a 400k-point torus k=1 43 / 56, k=4 97 / 101, k=20
+// 193 / 180, k=32 259 / 241 (with a k and prefix each k <= 4 212 / 198); 300k of k=20 over 400k
+// points 706 / 671, 500k over a solid of 5M 1240 / 1290; and not where lists are long (height
+// field, 65536 queries k=1 219 / 149, 300k of k=20 1410 / 1140).
 struct WaveShape {
   int32_t lanes, per_wave;
 };

@@ -547,8 +547,8 @@ struct DevBuf {
 };
 
 // Values of a round that the host decides by.  A kernel writes them to pinned memory: one
-// launch and one wait, where a copy of each to pageable memory took 14 us (100k points, 120 rounds: a new cloud
-// built, uploaded and queried in 42 ms instead of 57).
+// launch and one wait, where a copy of each to pageable memory took 14 us (100k points, 120
+// rounds: a new cloud built, uploaded and queried in 42 ms instead of 57).
 struct Peek {
   const void *src[4];
   int32_t size[4];   // bytes, 0: none
