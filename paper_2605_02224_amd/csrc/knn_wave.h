@@ -530,7 +530,7 @@ __device__ __forceinline__ bool expand(const QueryArgs &a, WaveLds<DW, R> &w, co
     nslot += nc;
     wave_lds_sync();
     // ---- insert
-    uint32_t lost = kPadKey;   // keys that fall out of the lanes, in any
+    uint32_t lost = kPadKey;   // the keys that fall out of N, in any lane
     if (nc <= kWaveInsert) {
       // one by one: every position keeps the middle of its key, the one before and the new.
       // Once the last lane is full, within these keys or before, each pushes one out (an empty

@@ -117,14 +117,14 @@ inline int64_t wave_sort_min(const LaunchSize &l, bool planes) {
 // Whether the rows of a launch (a batch's class) of nq queries gather candidates: it takes a third
 // fewer instructions, but rows wait for each other's merges, which only other wavefronts' work
 // hides, and short rows have few lists to take meanwhile.  ms per launch over a 1M-point torus,
-// step by step / gathered: k=16 1M queries 1.95 / 1.79, 262144 0.567 / 0.538, 131072 0.316 / 0.337;
+// step by step / gathered: k=16 1M queries 1.99 / 1.75, 262144 0.599 / 0.541, 131072 0.316 / 0.337;
 // k=8 1M queries 1.39 / 1.40.  Such rows know no merge threshold.
 constexpr bool gather_rows(int32_t k, int64_t nq) { return k > 8 && nq >= 196608; }
 
 // How the wave kernel lays the queries out: lanes per query in the descent, and queries per
 // wavefront (at most 64 / lanes; a second one only once every resident wavefront has one).
 // Eight queries a wavefront pay for short rows, and for bucketed launches over clouds past the
-// caches, 8 lanes / 16, us: 65536 queries over a 400k-point torus k=1 43 / 56, k=4 97 / 101, k=20
+// caches, 8 lanes / 16, us: 65536 queries over a 400k-point torus k=1 43 / 56, k=4 98 / 101, k=20
 // 193 / 180, k=32 259 / 241 (with a k and prefix each k <= 4 212 / 198); 300k of k=20 over 400k
 // points 706 / 671, 500k over a solid of 5M 1240 / 1290; and not where lists are long (height
 // field, 65536 queries k=1 219 / 149, 300k of k=20 1410 / 1140).

@@ -333,8 +333,8 @@ void knn_batch_flat_kernel(const BatchHeader *h, const QueryArgs *reqs, const Ba
 
 // The same launch by the wave kernel's walk, for classes of k > 16 whose requests all search
 // their whole cloud: four descents side by side, then the four expansions.  8 requests over
-// clouds of 20k points, rows / waves, ms: k = 64, 65536 queries each 4.04 / 2.70, 256 each 0.202
-// / 0.175; k = 32 1.64 / 1.42 and 0.107 / 0.094; k = 20 1.12 / 1.01 and 0.083 / 0.077.  In
+// clouds of 20k points, rows / waves, ms: k = 64, 65536 queries each 4.10 / 2.61, 256 each 0.200
+// / 0.153; k = 32 1.67 / 1.40 and 0.103 / 0.091; k = 20 1.13 / 1.00 and 0.081 / 0.074.  In
 // prefixes its batches of lists run half empty (see walk_for()): those classes go by rows.
 template <int S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8)))
