@@ -66,13 +66,13 @@ inline bool hub_lists(const LaunchSize &l) {
 // 200000 k <= 4 331 / 322 / 317 (367 / 343 / 367), k <= 16 464 / 476 / 444 (503 / 453 / 514);
 // 262144 k <= 4, bucketed 379 / 428 / 417 (417 / 434 / 454); 500k queries k <= 16 856 / 973 / 883
 // (927 / 870 / 957), k <= 32 1399 / 1434 / 1153 (1449 / 1150 / 1231).
-// Few queries in a prefix, rows / waves, over 400k points on a torus and in a solid: 6500 queries
-// k=2, m=100k 18.0 / 22.0 and 19.5 / 21.4, k=4, m=24k 19.3 / 22.7 and 19.8 / 24.6; 8191 queries
-// k=8, m=4k 23.9 / 28.7 and 22.7 / 27.0.  Close to kSmallQueries with long rows a few slow queries
-// hold the waves up, depending on the draw, which bucketed rows share: 16384 queries k=32, m=100k
-// 122 / 149 near a torus, 123 / 110 in its box, 118 / 115 in a solid, m=20k 104 / 117; k=64
-// 249 / 304, 245 / 201, 238 / 239.  In most of the cloud (m=390k) waves are ahead: 127 / 93,
-// 144 / 98.
+// Few queries in a prefix, time of waves over rows, mean of 16 or 24 draws (prefixes of a half, a
+// quarter, a twentieth and a hundredth; torus, solid, sphere and height field of 400k points; in
+// the box and near): k=2 4200 queries 0.90-0.99, 5000 0.95-1.04, 6500 1.04-1.18, 8191 1.04-1.30;
+// k=4 0.89-0.96, 0.95-0.99, 0.95-1.11, 0.95-1.23; k=8 a twentieth and up 0.75-0.97, a hundredth 0.87,
+// 0.90, 1.01, 1.10; 8192 and up (rows bucketed) 0.40-0.92.  k=32 and 64 2048 queries 0.52-0.55, 8192
+// 0.60-0.66, 14000 0.81-0.85, 16384 0.86-0.93: single draws reach 1.3 there (a few slow queries hold
+// the waves up, which bucketed rows share).
 // Long lists: 200k queries with a k and prefix each over a height field (longest list 2755), all
 // 400k points: k <= 32 rows 1094, waves 912, scan 1073; k <= 4 563 / 526 / 695.  With a hub, larger
 // launches go by rows but for k = 1, and for k <= 16 up to kLargeQueries: a sphere and its centre
@@ -85,13 +85,11 @@ inline Walk walk_for(const LaunchSize &l) {
     return l.kmax <= 16 && l.m >= l.n && l.nq <= kLargeQueries ? Walk::kWaves : Walk::kRows;
   }
   const bool uniform = !l.per_query, prefix = uniform && l.m < l.n;
-  if (prefix && l.kmax > 1) {
-    // as many wavefronts as are resident at once, each on one short query: rows, four to a
-    // wavefront and not bucketed either, issue less
-    if (l.nq > 4096 && l.nq < kSortMinQueries && (l.kmax <= 4 || (l.kmax <= 16 && l.m < l.n / 32)))
-      return Walk::kRows;
-    if (l.nq > 15360 && l.nq <= kSmallQueries && l.kmax > 16 && l.m <= l.n / 2) return Walk::kRows;
-  }
+  // as many wavefronts as are resident at once, each on one short query: rows, four to a
+  // wavefront and not bucketed either, issue less
+  if (prefix && l.kmax > 1 && l.nq < kSortMinQueries &&
+      (l.kmax <= 4 ? l.nq > 5000 : l.kmax <= 8 && l.nq > 6500 && l.m < l.n / 32))
+    return Walk::kRows;
   if (l.nq <= kSmallQueries || (uniform && l.kmax == 1)) return Walk::kWaves;
   if (!uniform) {
     if (l.nq <= kLargeQueries || (long_lists(l) && l.nq < kWaveSortQueries)) return Walk::kWaves;

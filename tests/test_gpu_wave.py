@@ -347,7 +347,7 @@ def test_upload_takes_the_arena_alone(env, n):
 ROUTES = {
     "gathered_k9": (196608, 9, None), "gathered_k16": (196609, 16, None),
     "gathered_prefix": (196608, 12, 700), "rows_k2": (65537, 2, None), "rows_k8": (70001, 8, None),
-    "rows_k16": (70003, 16, None), "rows_prefix_k3": (6001, 3, 1700), "rows_prefix_k16": (8191, 16, 120),
+    "rows_k16": (70003, 16, None), "rows_prefix_k3": (6001, 3, 1700), "rows_prefix_k8": (8191, 8, 120),
     "rows_prefix_k17": (20001, 17, 1500), "rows_prefix_k33": (20002, 33, 1500),
     "rows_prefix_k64": (20003, 64, 1500), "rows_one_site_more": (20001, 64, 65),
     "rows_as_many": (20001, 32, 32), "waves_k20": (70001, 20, None), "waves_k64": (131073, 64, None),
